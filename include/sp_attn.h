@@ -359,6 +359,9 @@ sp_status sp_f32_to_bf16(const float* src, void* dst, int64_t n, void* stream);
  *       first (its rows see the fewest keys).
  *   SP_OP_BWD, dK/dV items: {k_begin, k_end, q_begin, q_end, delta, head,
  *       kv_head, 1}.
+ * A launch of few items splits each of them over S workgroups (row items: S =
+ * 1, 2 or 4, 256 / S rows each), which follow each other on the item's XCD;
+ * the list is the same.
  * Writes at most `capacity` items to `items` (may be NULL) and the total
  * count to *n_items.  Not listed: the zero fills of dummy query slots (and,
  * for one query head per KV head, of KV heads no real query head reads),

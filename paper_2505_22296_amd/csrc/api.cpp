@@ -269,9 +269,40 @@ void sort_items(std::vector<Item>& items, std::vector<int32_t>& out, size_t n_fr
   }
 }
 
-// Row-tile items (forward, ring step, dQ).
-void schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN, bool include_empty,
-                   std::vector<int32_t>& out, size_t n_front) {
+// Workgroups an item's rows are split over, for launches whose items of 256
+// rows would leave CUs idle: with S workgroups an item each owns 256 / S rows
+// and its eight wavefronts are S key groups that walk the keys side by side,
+// so an item takes 1 / S of the steps but every key tile is staged for fewer
+// rows.  Modelled in steps of one workgroup: a step of S = 2 / 4 costs `rel`
+// times one of S = 1 (the forward of a full chip at D = 128: 1.45, 1.75 and
+// 2.3 us a 64-key step, 1.3, 1.45 and 2.1 us where 64 or 128 workgroups run),
+// a workgroup's start and end `kStartSteps`.  The time is bounded below by
+// the average load of the 256 CUs and, for each k, by k + 1 times the
+// (256 k)-th longest of the workgroups (two of the first 257 share a CU); the
+// S with the lowest bound is taken.  `sorted`: longest first.
+int row_split(const std::vector<Item>& sorted) {
+  constexpr double kCus = 256, kStartSteps = 3, kRel[3] = {1.0, 1.22, 1.6};
+  double total = 0;
+  for (const Item& it : sorted) total += (double)it.cost;
+  const size_t N = sorted.size();
+  int best = 1;
+  double best_t = 0;
+  for (int i = 0, S = 1; i < 3; ++i, S *= 2) {
+    double t = (total * kRel[i] + (double)N * S * kStartSteps) / kCus;
+    for (size_t k = 0; k * 256 < N * S; ++k)
+      t = std::max(t, (double)(k + 1) *
+                          ((double)sorted[k * 256 / S].cost / S * kRel[i] + kStartSteps));
+    if (i == 0 || t < best_t) {
+      best = S;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+// Row-tile items (forward, ring step, dQ).  Returns the split of the launch.
+int schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN, bool include_empty,
+                  std::vector<int32_t>& out, size_t n_front) {
   std::vector<Item> items;
   for (int y = 0; y < p.n_real; ++y) {
     for (const Seg& g : p.segs) {
@@ -297,7 +328,8 @@ void schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN, bool
       for (int a = p.q_pad; a < d->T_q; a += BM)
         items.push_back(Item{{a, std::min(a + BM, d->T_q), 0, 0, 0, y, p.kv_of[y], 0}, 0});
   }
-  sort_items(items, out, n_front, true);
+  sort_items(items, out, n_front, true);  // (leaves `items` longest first)
+  return row_split(items);
 }
 
 // Key-tile items (dK / dV).  Every key of every real head gets exactly one item.
@@ -732,7 +764,8 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
   const bool include_empty = !ring || init || o_out;
   std::vector<int32_t> items;
   const std::vector<int32_t> fills = include_empty ? row_fills(d, p) : std::vector<int32_t>();
-  schedule_rows(d, p, spk::kFwdBM, spk::kFwdBN, include_empty, items, fills.size() / kItemInts);
+  const int split = schedule_rows(d, p, spk::kFwdBM, spk::kFwdBN, include_empty, items,
+                                  fills.size() / kItemInts);
   prepend(fills, items);
   const int n_items = (int)(items.size() / kItemInts);
   hipStream_t st = (hipStream_t)stream;
@@ -765,7 +798,8 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
     a.scale_log2 = d->softmax_scale * 1.4426950408889634f;
     a.causal = d->causal;
     a.init = init;
-    SP_HIP(spk::launch_attn_fwd(a, n_items, p.D, ring, st));
+    a.n_items = n_items;
+    SP_HIP(spk::launch_attn_fwd(a, split, p.D, ring, st));
   }
   return SP_OK;
 }

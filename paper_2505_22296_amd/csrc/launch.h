@@ -98,6 +98,7 @@ struct FwdArgs {
   int T_q, T_k, H, Hkv;
   float scale_log2;    // softmax_scale * log2(e)
   int causal, init;
+  int n_items;
 };
 
 struct DqArgs {
@@ -155,7 +156,8 @@ hipError_t launch_rowdot(const void* o, const void* dout, const float* lse, floa
 hipError_t launch_reduce_kv(const float* part_k, const float* part_v, void* dk, void* dv,
                             const ReduceArgs& a, hipStream_t st);
 
-hipError_t launch_attn_fwd(const FwdArgs& a, int n_items, int D, bool merge, hipStream_t st);
+// `split` workgroups an item (1, 2 or 4): 256 / split rows each
+hipError_t launch_attn_fwd(const FwdArgs& a, int split, int D, bool merge, hipStream_t st);
 hipError_t launch_attn_dq(const DqArgs& a, int n_items, int D, hipStream_t st);
 hipError_t launch_attn_dkdv(const DkdvArgs& a, int n_items, int D, hipStream_t st);
 
