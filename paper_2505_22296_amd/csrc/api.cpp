@@ -269,29 +269,40 @@ void sort_items(std::vector<Item>& items, std::vector<int32_t>& out, size_t n_fr
   }
 }
 
-// Workgroups an item's rows are split over, for launches whose items of 256
-// rows would leave CUs idle: with S workgroups an item each owns 256 / S rows
-// and its eight wavefronts are S key groups that walk the keys side by side,
-// so an item takes 1 / S of the steps but every key tile is staged for fewer
-// rows.  Modelled in steps of one workgroup: a step of S = 2 / 4 costs `rel`
-// times one of S = 1 (the forward of a full chip at D = 128: 1.45, 1.75 and
-// 2.3 us a 64-key step, 1.3, 1.45 and 2.1 us where 64 or 128 workgroups run),
-// a workgroup's start and end `kStartSteps`.  The time is bounded below by
-// the average load of the 256 CUs and, for each k, by k + 1 times the
-// (256 k)-th longest of the workgroups (two of the first 257 share a CU); the
-// S with the lowest bound is taken.  `sorted`: longest first.
-int row_split(const std::vector<Item>& sorted) {
-  constexpr double kCus = 256, kStartSteps = 3, kRel[3] = {1.0, 1.22, 1.6};
+// Workgroups an item is split over, for launches whose items would leave CUs
+// idle.  With S workgroups an item, each owns 1 / S of its rows (keys) and its
+// wavefronts form S groups that walk the keys (rows) side by side: 1 / S of
+// the steps, but every staged tile serves 1 / S of the rows.  Modelled in
+// steps of an unsplit workgroup: `rel[i]`, a step's cost at S = 2^i against
+// one at S = 1 (28 heads of 4096 rows at D = 128, every CU busy: forward 122,
+// 150, 193 us; dQ 163, 190, 234; dK/dV 229, 280), and `start`, what a
+// workgroup's start and end cost (about 6 us).  A launch takes at least the
+// average load of the 256 CUs and, for each k, k + 1 times its (256 k)-th
+// longest workgroup (of the first 256 k + 1, k + 1 share a CU); the S with the
+// lowest such bound is taken.  The largest items of small launches decide:
+// 4 heads of 4096 rows take S = 4 in the forward (92 -> 43 us), 28 heads of
+// 4096 rows stay whole.  `sorted`: longest first.
+struct SplitModel {
+  int n;  // S = 1, 2, .. 2^(n-1)
+  double start, rel[3];
+};
+constexpr SplitModel kSplitFwd{3, 4, {1.0, 1.22, 1.6}};   // steps of 64 keys
+constexpr SplitModel kSplitDq{3, 8, {1.0, 1.15, 1.45}};   // steps of 32 keys
+constexpr SplitModel kSplitDkdv{2, 8, {1.0, 1.22, 0}};    // steps of 32 rows
+
+int choose_split(const std::vector<Item>& sorted, const SplitModel& m) {
+  constexpr size_t kCus = 256;
   double total = 0;
   for (const Item& it : sorted) total += (double)it.cost;
   const size_t N = sorted.size();
   int best = 1;
   double best_t = 0;
-  for (int i = 0, S = 1; i < 3; ++i, S *= 2) {
-    double t = (total * kRel[i] + (double)N * S * kStartSteps) / kCus;
-    for (size_t k = 0; k * 256 < N * S; ++k)
+  for (int i = 0; i < m.n; ++i) {
+    const int S = 1 << i;
+    double t = (total * m.rel[i] + (double)(N * S) * m.start) / kCus;
+    for (size_t k = 0; k * kCus < N * S; ++k)
       t = std::max(t, (double)(k + 1) *
-                          ((double)sorted[k * 256 / S].cost / S * kRel[i] + kStartSteps));
+                          ((double)sorted[k * kCus / S].cost / S * m.rel[i] + m.start));
     if (i == 0 || t < best_t) {
       best = S;
       best_t = t;
@@ -301,8 +312,8 @@ int row_split(const std::vector<Item>& sorted) {
 }
 
 // Row-tile items (forward, ring step, dQ).  Returns the split of the launch.
-int schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN, bool include_empty,
-                  std::vector<int32_t>& out, size_t n_front) {
+int schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN, const SplitModel& m,
+                  bool include_empty, std::vector<int32_t>& out, size_t n_front) {
   std::vector<Item> items;
   for (int y = 0; y < p.n_real; ++y) {
     for (const Seg& g : p.segs) {
@@ -329,12 +340,13 @@ int schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN, bool 
         items.push_back(Item{{a, std::min(a + BM, d->T_q), 0, 0, 0, y, p.kv_of[y], 0}, 0});
   }
   sort_items(items, out, n_front, true);  // (leaves `items` longest first)
-  return row_split(items);
+  return choose_split(items, m);
 }
 
-// Key-tile items (dK / dV).  Every key of every real head gets exactly one item.
-void schedule_keys(const sp_attn_desc* d, const Problem& p, int BNK, int BQ,
-                   std::vector<int32_t>& out, size_t n_front) {
+// Key-tile items (dK / dV).  Every key of every real head gets exactly one
+// item.  Returns the split of the launch.
+int schedule_keys(const sp_attn_desc* d, const Problem& p, int BNK, int BQ,
+                  std::vector<int32_t>& out, size_t n_front) {
   std::vector<Item> items;
   for (int y = 0; y < p.n_real; ++y) {
     for (const Seg& g : p.segs_k) {
@@ -352,6 +364,7 @@ void schedule_keys(const sp_attn_desc* d, const Problem& p, int BNK, int BQ,
       items.push_back(Item{{a, std::min(a + BNK, d->T_k), 0, 0, 0, y, p.kv_of[y], 1}, 0});
   }
   sort_items(items, out, n_front, false);
+  return choose_split(items, kSplitDkdv);
 }
 
 // Zero fills as work items of the same launch (no extra kernels): dummy
@@ -682,7 +695,7 @@ sp_status sp_attn_schedule(const sp_attn_desc* desc, int32_t op, int32_t* items,
   // in launch order: the fill items that precede the listed ones there
   // shift the workgroup -> XCD map
   if (op == SP_OP_FWD || op == SP_OP_RING_STEP)
-    schedule_rows(desc, p, spk::kFwdBM, spk::kFwdBN, true, v,
+    schedule_rows(desc, p, spk::kFwdBM, spk::kFwdBN, kSplitFwd, true, v,
                   row_fills(desc, p).size() / kItemInts);
   else if (op == SP_OP_BWD)
     schedule_keys(desc, p, spk::kDkdvBN, spk::kDkdvBQ, v, key_fills(desc, p).size() / kItemInts);
@@ -764,8 +777,8 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
   const bool include_empty = !ring || init || o_out;
   std::vector<int32_t> items;
   const std::vector<int32_t> fills = include_empty ? row_fills(d, p) : std::vector<int32_t>();
-  const int split = schedule_rows(d, p, spk::kFwdBM, spk::kFwdBN, include_empty, items,
-                                  fills.size() / kItemInts);
+  const int split = schedule_rows(d, p, spk::kFwdBM, spk::kFwdBN, kSplitFwd, include_empty,
+                                  items, fills.size() / kItemInts);
   prepend(fills, items);
   const int n_items = (int)(items.size() / kItemInts);
   hipStream_t st = (hipStream_t)stream;
@@ -848,9 +861,11 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
   // a dq_acc's dummy slots stay untouched
   const std::vector<int32_t> fq = dq ? row_fills(d, p) : std::vector<int32_t>();
   const std::vector<int32_t> fkv = key_fills(d, p);
-  schedule_rows(d, p, spk::kDqBM, spk::kDqBN, true, it_dq, fq.size() / kItemInts);
+  const int split_q =
+      schedule_rows(d, p, spk::kDqBM, spk::kDqBN, kSplitDq, true, it_dq, fq.size() / kItemInts);
   prepend(fq, it_dq);
-  schedule_keys(d, p, spk::kDkdvBN, spk::kDkdvBQ, it_kv, fkv.size() / kItemInts);
+  const int split_k =
+      schedule_keys(d, p, spk::kDkdvBN, spk::kDkdvBQ, it_kv, fkv.size() / kItemInts);
   prepend(fkv, it_kv);
   const size_t na = it_dq.size() / kItemInts, nb = it_kv.size() / kItemInts;
   Layout L = layout_for(d, p, SP_OP_BWD, na, nb);
@@ -881,7 +896,8 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     a.items = (const int32_t*)at(ws, L.items_dq);
     a.T_q = d->T_q; a.T_k = d->T_k; a.H = d->H_loc; a.Hkv = d->Hkv_loc;
     a.scale_log2 = sl2; a.scale = d->softmax_scale; a.causal = d->causal;
-    SP_HIP(spk::launch_attn_dq(a, (int)na, D, st));
+    a.n_items = (int)na;
+    SP_HIP(spk::launch_attn_dq(a, split_q, D, st));
 
     spk::DkdvArgs b{};
     b.q = (const uint16_t*)q;
@@ -893,7 +909,8 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     b.items = (const int32_t*)at(ws, L.items_kv);
     b.T_q = d->T_q; b.T_k = d->T_k; b.H = d->H_loc; b.Hkv = d->Hkv_loc;
     b.scale_log2 = sl2; b.scale = d->softmax_scale; b.causal = d->causal; b.direct = p.direct;
-    SP_HIP(spk::launch_attn_dkdv(b, (int)nb, D, st));
+    b.n_items = (int)nb;
+    SP_HIP(spk::launch_attn_dkdv(b, split_k, D, st));
     if (!p.direct && p.n_real > 0) {
       spk::ReduceArgs r{};
       r.T = d->T_k; r.Hkv = d->Hkv_loc; r.D = D;

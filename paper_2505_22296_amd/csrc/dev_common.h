@@ -208,6 +208,28 @@ SP_DEV void load_item(const int32_t* items, int64_t pos, int32_t (&v)[8]) {
   for (int j = 0; j < 8; ++j) v[j] = p[j];
 }
 
+// Launches that split every work item over S workgroups: workgroup b runs on
+// XCD b % 8, and an XCD's S consecutive workgroups share one item of its list
+// positions, the item's last rows first (under a causal mask they see the most
+// keys).  The grid holds S workgroups for every position, rounded up to eight
+// positions (split_grid); false past the list.
+template <int S>
+SP_DEV bool split_pos(int n_items, int& pos, int& sub) {
+  const int j = blockIdx.x >> 3;  // the XCD's j-th workgroup
+  pos = (j / S) * 8 + (blockIdx.x & 7);
+  sub = S - 1 - j % S;
+  return pos < n_items;
+}
+// Rows (keys) [b, e) of the item that workgroup `sub` of it owns: `tile` of
+// them, or an even share of a zero fill; false if there are none.
+template <int S>
+SP_DEV bool split_rows(bool fill, int tile, int sub, int& b, int& e) {
+  const int n = fill ? (e - b + S - 1) / S : tile;
+  b += sub * n;
+  e = min(e, b + n);
+  return b < e;
+}
+
 // Zero-fill work items (dummy query slots, unread KV heads): the whole
 // workgroup writes rows [r0, r1) of head h of a [T, H, D] tensor with 16-byte
 // stores, block-strided.  bf16 (zero = +0) and float32 variants.

@@ -31,52 +31,69 @@ namespace {
 constexpr int NT = 256;
 
 // ------------------------------------------------------------------- dQ
-// Workgroup = NWQ wavefronts = 32*NWQ query rows of one head.  LDS stage:
-// K and V tiles [32 keys][D] in the blocked layout of dev_common.h (K^T
-// fragments are transposing reads of the K tile), filled by DMA in 1 KB
-// blocks spread over the wavefronts; NSTQ tiles resident, barrier every
-// TPBQ tiles.
-constexpr int NWQ = kDqWaves, NTQ = 64 * NWQ, NSTQ = kDqStages, TPBQ = kDqTilesPerSync;
-static_assert(kDqBM == 32 * NWQ && NSTQ % TPBQ == 0 && NSTQ >= 2 * TPBQ, "dq tiling");
+// Workgroup = NWQ wavefronts = KW key groups of RW = NWQ / KW wavefronts; row
+// group w % RW owns 32 query rows of one head, key group w / RW every KW-th
+// key tile (KW = 1: 256 rows a workgroup; KW = 2, 4 for launches of few items,
+// as in the forward).  LDS stage: the groups' K and V tiles [32 keys][D] in
+// the blocked layout of dev_common.h (K^T fragments are transposing reads of
+// the K tile), filled by DMA in 1 KB blocks spread over the group's
+// wavefronts; NST stages resident, barrier every TPB stages.
+// 4 heads on one causal sequence, D = 128, KW = 1 / 2 / 4: 1024 rows 41 / 28 /
+// 22 us, 4096 rows 130 / 77 / 53, 16384 rows 532 / 391 / 460; 28 heads of 4096
+// rows 163 / 190 / 234 us.
+constexpr int NWQ = kDqWaves, NTQ = 64 * NWQ;
+static_assert(kDqBM == 32 * NWQ, "dq tiling");
 
-template <int D>
+template <int D, int KW>
 struct DqStage {
+  static constexpr int RW = NWQ / KW;
   static constexpr int BN = kDqBN;
+  static constexpr int NST = KW * D > 256 ? 2 : kDqStages;
+  static constexpr int TPB = KW * D > 256 ? 1 : kDqTilesPerSync;
+  static_assert(NST % TPB == 0 && NST >= 2 * TPB, "dq pipeline");
   static constexpr int SUB = BN * 4;             // chunks per sub-tile [BN][32]
   static constexpr int RB = BN * (D / 8) / 64;   // 1 KB blocks of a tile
   static constexpr int NB = 2 * RB;
-  static constexpr int NBW = (NB + NWQ - 1) / NWQ;  // blocks per wavefront (tail ones junk)
-  static constexpr int OFF_V = RB * 64, STAGE = NB * 64;
-  static constexpr int JUNK = NSTQ * STAGE, SMEM = JUNK + 64;
-  // 0 = K, 1 = V, 2 = unused slot (copied to the junk block)
-  static SP_DEV int kind(int b) { return b < RB ? 0 : b < NB ? 1 : 2; }
+  static constexpr int NBW = NB / RW;            // blocks per wavefront
+  static_assert(NB % RW == 0, "DMA blocks per wavefront");
+  static constexpr int OFF_V = RB * 64, TILE = NB * 64, STAGE = KW * TILE;
+  // dQ^T of every wavefront, exchanged through the same LDS (KW > 1)
+  static constexpr int NQ = D / 8, XCH = KW > 1 ? NWQ * NQ * 64 : 0;
+  static constexpr int SMEM = NST * STAGE > XCH ? NST * STAGE : XCH;
 };
 
-template <int D>
+template <int D, int KW>
 __global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
-  using S = DqStage<D>;
-  constexpr int BN = S::BN, KS = D / 16, DB = D / 32;
+  using S = DqStage<D, KW>;
+  constexpr int RW = S::RW, BN = S::BN, KS = D / 16, DB = D / 32, NST = S::NST, TPB = S::TPB;
   constexpr int NBW = S::NBW, STAGE = S::STAGE, SUB = S::SUB;
 
   __shared__ u32x4 smem[S::SMEM];
 
-  const int32_t* it = a.items + (int64_t)blockIdx.x * kItemInts;
-  const int q0 = it[0], q1 = it[1], k0 = it[2], k1 = it[3], delta = it[4], head = it[5],
-            kvh = it[6];
+  int pos = blockIdx.x, sub = 0;
+  if constexpr (KW > 1)
+    if (!split_pos<KW>(a.n_items, pos, sub)) return;
+  const int32_t* it = a.items + (int64_t)pos * kItemInts;
+  int q0 = it[0], q1 = it[1], k1 = it[3];
+  const int k0 = it[2], delta = it[4], head = it[5], kvh = it[6];
   const int tid = threadIdx.x;
+  if constexpr (KW > 1) {
+    if (!split_rows<KW>(it[7] == kItemFillQ, 32 * RW, sub, q0, q1)) return;
+    if (a.causal) k1 = max(k0, min(k1, q1 + delta));
+  }
   if (it[7] == kItemFillQ) {  // dummy slot of a bf16 dQ: +0
     fill_rows_bf16(a.dq, q0, q1, a.H, head, D, tid, NTQ);
     return;
   }
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, hh = lane >> 5, l32 = lane & 31;
-  const int row = q0 + w * 32 + l32;
+  const int rg = KW > 1 ? w % RW : w, kg = KW > 1 ? w / RW : 0;
+  const int wr0 = q0 + rg * 32;  // the wavefront's first row
+  const int row = wr0 + l32;
   const bool row_ok = row < q1;
   const int lrow = row_ok ? row : q0;
-  const int wave_rows = min(32, q1 - q0 - w * 32);
-  const int wave_kmax = wave_rows <= 0 ? -1
-                        : a.causal     ? min(k1, q0 + w * 32 + wave_rows + delta)
-                                       : k1;
+  const int wave_rows = min(32, q1 - wr0);
+  const int wave_kmax = wave_rows <= 0 ? -1 : a.causal ? min(k1, wr0 + wave_rows + delta) : k1;
 
   u32x4 qf[KS], df[KS];
   {
@@ -104,40 +121,31 @@ __global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
     for (int r = 0; r < 16; ++r) acc[d][r] = 0.f;
 
   const int kt_first = k0 & ~7;
-  const int n_tiles = (k1 > k0) ? (k1 - kt_first + BN - 1) / BN : 0;
+  // stages of KW tiles
+  const int n_tiles = (k1 > k0) ? (k1 - kt_first + BN * KW - 1) / (BN * KW) : 0;
 
-  // Per-lane, tile-independent element offsets of this wavefront's DMA blocks
-  // w + NWQ*j (the block kinds are wave-uniform; K and V share shape and
-  // source row stride).
+  // The wavefront's DMA blocks are rg + RW*j of the K, then the V blocks; a
+  // block holds 16 rows of one 32-dim sub-tile, block b rows 16 (b % 2) .. of
+  // sub-tile b / 2.  RW is even, so the lane's row and byte offset in the
+  // sub-tile are the same for all of them; the sub-tile goes to the scalar
+  // base (K and V share shape and source row stride).
+  static_assert(SUB == 128 && RW % 2 == 0, "two blocks a sub-tile");
   const int kstride = a.Hkv * D;
-  int off[NBW], key_of[NBW];
-#pragma unroll
-  for (int j = 0; j < NBW; ++j) {
-    const int b = w + NWQ * j;
-    const int k = S::kind(b);
-    const int t = (k == 1 ? b - S::RB : k == 0 ? b : 0) * 64 + lane;
-    const int ts = t % SUB, r = ts / 4;
-    key_of[j] = r;
-    off[j] = 2 * (r * kstride + (t / SUB) * 32 + blk_chunk(r, ts % 4) * 8);  // bytes
-  }
+  const int key_of = (rg & 1) * 16 + (lane >> 2);
+  const int off = 2 * (key_of * kstride + blk_chunk(key_of, lane & 3) * 8);  // bytes
   const uint16_t* kbase = a.k + (int64_t)kvh * D;
   const uint16_t* vbase = a.v + (int64_t)kvh * D;
   auto issue = [&](int n) {
-    const int kt = kt_first + n * BN;
-    u32x4* stg = smem + (n % NSTQ) * STAGE;
+    const int kt = kt_first + (n * KW + kg) * BN;
+    if (KW > 1 && kt >= k1) return;  // the key group has no tile in the last stage
+    u32x4* stg = smem + (n % NST) * STAGE + kg * S::TILE;
     const int64_t rowoff = (int64_t)kt * kstride;
-    auto copy = [&](int j, int o) {
-      const int b = w + NWQ * j;
-      const int k = S::kind(b);
-      dma16s((k == 1 ? vbase : kbase) + rowoff, o, k == 2 ? smem + S::JUNK : stg + b * 64);
-    };
-    if (kt + BN <= k1) {
+    // keys past k1 (masked) are clamped to k1-1
+    const int o = kt + BN <= k1 ? off : off + 2 * (min(kt + key_of, k1 - 1) - kt - key_of) * kstride;
 #pragma unroll
-      for (int j = 0; j < NBW; ++j) copy(j, off[j]);
-    } else {  // keys past k1 (masked) are clamped to k1-1
-#pragma unroll
-      for (int j = 0; j < NBW; ++j)
-        copy(j, off[j] + 2 * (min(kt + key_of[j], k1 - 1) - kt - key_of[j]) * kstride);
+    for (int j = 0; j < NBW; ++j) {
+      const int b = rg + RW * j, bb = b % S::RB;
+      dma16s((b < S::RB ? kbase : vbase) + rowoff + (bb >> 1) * 32, o, stg + b * 64);
     }
   };
   // lane-constant LDS offsets of the fragments (see the forward kernel)
@@ -145,26 +153,26 @@ __global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
   const int kf0 = kr * 4 + blk_chunk(kr, hh), kf1 = kr * 4 + blk_chunk(kr, 2 + hh);
   const int kt0 = blk_tr_off(lane), kt1 = blk_tr_off2(lane);
 
-  for (int n = 0; n < NSTQ - TPBQ && n < n_tiles; ++n) issue(n);
+  for (int n = 0; n < NST - TPB && n < n_tiles; ++n) issue(n);
 
-  for (int n0 = 0; n0 < n_tiles; n0 += NSTQ) {
+  for (int n0 = 0; n0 < n_tiles; n0 += NST) {
 #pragma unroll
-    for (int u = 0; u < NSTQ; ++u) {
+    for (int u = 0; u < NST; ++u) {
       const int n = n0 + u;
       if (n >= n_tiles) break;
-      if (u % TPBQ == 0) {
-        // tiles n .. n+TPBQ-1 landed; the stages of tiles n-TPBQ .. n-1 are
-        // free and receive tiles n+NSTQ-TPBQ ..
-        const int issued = min(n_tiles, n + NSTQ - TPBQ);
-        wait_batches<NBW, NSTQ - 2 * TPBQ>(issued - min(n_tiles, n + TPBQ));
+      if (u % TPB == 0) {
+        // stages n .. n+TPB-1 landed; the memory of stages n-TPB .. n-1 is
+        // free and receives stages n+NST-TPB ..
+        const int issued = min(n_tiles, n + NST - TPB);
+        wait_batches<NBW, NST - 2 * TPB>(issued - min(n_tiles, n + TPB));
         __syncthreads();
 #pragma unroll
-        for (int t = 0; t < TPBQ; ++t)
-          if (n + NSTQ - TPBQ + t < n_tiles) issue(n + NSTQ - TPBQ + t);
+        for (int t = 0; t < TPB; ++t)
+          if (n + NST - TPB + t < n_tiles) issue(n + NST - TPB + t);
       }
-      const int kt = kt_first + n * BN;
+      const int kt = kt_first + (n * KW + kg) * BN;
       if (kt >= wave_kmax) continue;  // wholly past this wavefront's rows
-      const u32x4* stg = smem + u * STAGE;
+      const u32x4* stg = smem + u * STAGE + kg * S::TILE;
 
       // K and V fragments of the tile, all read before the first MFMA
       u32x4 kfr[KS], vfr[KS];
@@ -175,7 +183,19 @@ __global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
         vfr[ks] = stg[S::OFF_V + fo];
       }
       __builtin_amdgcn_sched_barrier(0);
-      f32x16 s, dp = ndv;  // dP starts from -D, so the MFMAs leave dP - D
+      // dP starts from -D, so the MFMAs leave dP - D.  At D = 128, KW = 4 fills
+      // the vector anew (16 moves a tile): held, it spills a Q fragment whose
+      // reload waits for every copy in flight (4 heads x 4096 rows: 66 -> 53
+      // us; without that spill the moves cost 2-5%)
+      f32x16 s, dp;
+      if constexpr (KW == 4 && D == 128) {
+        float nd = ndrow;
+        asm volatile("" : "+v"(nd));
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dp[r] = nd;
+      } else {
+        dp = ndv;
+      }
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
@@ -195,7 +215,7 @@ __global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
           ktr[d * 2 + ks] = u32x4{lo[0], lo[1], hi[0], hi[1]};
         }
       __builtin_amdgcn_sched_barrier(0);
-      const bool need_mask = (kt < k0) | (kt + BN > k1) | (a.causal & (kt + BN - 1 > q0 + w * 32 + delta));
+      const bool need_mask = (kt < k0) | (kt + BN > k1) | (a.causal & (kt + BN - 1 > wr0 + delta));
       if (need_mask) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -221,38 +241,61 @@ __global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
     }
   }
 
+  // quad i of the row: 4 dims at (i >> 2) * 32 + (i & 3) * 8 + hh * 4; the key
+  // groups share out the quads of a row, each summed in group order
+  constexpr int NQW = S::NQ / KW;
+  float sum[NQW][4];
+  if constexpr (KW == 1) {
+#pragma unroll
+    for (int i = 0; i < NQW; ++i)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) sum[i][x] = acc[i >> 2][(i & 3) * 4 + x];
+  } else {
+    __syncthreads();  // (every copy has landed: the last stage's barrier waited for it)
+    f32x4* xs = (f32x4*)smem;
+#pragma unroll
+    for (int i = 0; i < S::NQ; ++i)
+      xs[(w * S::NQ + i) * 64 + lane] = f32x4{acc[i >> 2][(i & 3) * 4], acc[i >> 2][(i & 3) * 4 + 1],
+                                              acc[i >> 2][(i & 3) * 4 + 2], acc[i >> 2][(i & 3) * 4 + 3]};
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NQW; ++i) {
+#pragma unroll
+      for (int p = 0; p < KW; ++p) {
+        const f32x4 v = xs[((rg + RW * p) * S::NQ + kg * NQW + i) * 64 + lane];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) sum[i][x] = p ? sum[i][x] + v[x] : v[x];
+      }
+    }
+  }
   if (!row_ok) return;
   const float sc = a.scale;
   const int64_t base = ((int64_t)row * a.H + head) * D + hh * 4;
+  auto dim = [&](int i) { return ((kg * NQW + i) >> 2) * 32 + ((kg * NQW + i) & 3) * 8; };
   if (a.dq_acc) {  // ring: accumulate; the last chunk emits bf16 instead
     // every accumulator value is loaded before the first store: the stores
     // (through dq or dq_acc) could alias later loads for all the compiler
     // knows, which would serialize one memory round trip per 16 bytes
-    float4 old[DB * 4];
+    float4 old[NQW];
 #pragma unroll
-    for (int i = 0; i < DB * 4; ++i)
+    for (int i = 0; i < NQW; ++i)
       old[i] = a.dq_init ? make_float4(0.f, 0.f, 0.f, 0.f)
-                         : *(const float4*)(a.dq_acc + base + (i >> 2) * 32 + (i & 3) * 8);
+                         : *(const float4*)(a.dq_acc + base + dim(i));
 #pragma unroll
-    for (int d = 0; d < DB; ++d)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float4 o = old[d * 4 + j];
-        const float4 t = make_float4(o.x + acc[d][j * 4] * sc, o.y + acc[d][j * 4 + 1] * sc,
-                                     o.z + acc[d][j * 4 + 2] * sc, o.w + acc[d][j * 4 + 3] * sc);
-        if (a.dq)
-          *(u32x2*)(a.dq + base + d * 32 + j * 8) = pack_bf16x4(t.x, t.y, t.z, t.w);
-        else
-          *(float4*)(a.dq_acc + base + d * 32 + j * 8) = t;
-      }
+    for (int i = 0; i < NQW; ++i) {
+      const float4 o = old[i];
+      const float4 t = make_float4(o.x + sum[i][0] * sc, o.y + sum[i][1] * sc,
+                                   o.z + sum[i][2] * sc, o.w + sum[i][3] * sc);
+      if (a.dq)
+        *(u32x2*)(a.dq + base + dim(i)) = pack_bf16x4(t.x, t.y, t.z, t.w);
+      else
+        *(float4*)(a.dq_acc + base + dim(i)) = t;
+    }
   } else {
 #pragma unroll
-    for (int d = 0; d < DB; ++d)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *(u32x2*)(a.dq + base + d * 32 + j * 8) =
-            pack_bf16x4(acc[d][j * 4] * sc, acc[d][j * 4 + 1] * sc, acc[d][j * 4 + 2] * sc,
-                        acc[d][j * 4 + 3] * sc);
+    for (int i = 0; i < NQW; ++i)
+      *(u32x2*)(a.dq + base + dim(i)) =
+          pack_bf16x4(sum[i][0] * sc, sum[i][1] * sc, sum[i][2] * sc, sum[i][3] * sc);
   }
 }
 
@@ -289,9 +332,15 @@ struct DkdvStage {
   static SP_DEV int kind(int b) { return b < RB ? 0 : b < NB ? 1 : 2; }
 };
 
-template <int D, bool PWAVE>
+// RG row groups of NPF / RG pairs (RG = 2: an item's keys are split over two
+// workgroups of 64 keys, for launches of few items; 4 heads on one causal
+// sequence, D = 128, RG = 1 / 2: 1024 rows 33 / 24 us, 4096 rows 102 / 68,
+// 16384 rows 480 / 587 us): pair p owns keys k0 + 32 (p % (NPF / RG)) ..
+// +32 and row group p / (NPF / RG), the chunks c with c % RG == its row group.
+template <int D, bool PWAVE, int RG>
 SP_DEV void dkdv_body(const DkdvArgs& a, const int32_t (&it)[kItemInts], u32x4* smem, int w,
                       int lane) {
+  static_assert(TPBF % RG == 0, "every row group has a chunk in every group of chunks");
   using S = DkdvStage<D>;
   constexpr int BQ = S::BQ, KS = D / 16, DB = D / 32, SUB = S::SUB, NBW = S::NBW;
   constexpr int STAGE = S::STAGE;
@@ -299,7 +348,8 @@ SP_DEV void dkdv_body(const DkdvArgs& a, const int32_t (&it)[kItemInts], u32x4* 
             kvh = it[6];
   const int hh = lane >> 5, l32 = lane & 31;
   const int pr = PWAVE ? w : w - NPF;  // pair index
-  const int wk0 = k0 + pr * 32;
+  const int rgi = RG > 1 ? pr / (NPF / RG) : 0;
+  const int wk0 = k0 + (RG > 1 ? pr % (NPF / RG) : pr) * 32;
   const int key = wk0 + l32;
   const bool key_ok = key < k1;
   const int qc_first = qb & ~7;
@@ -477,36 +527,72 @@ SP_DEV void dkdv_body(const DkdvArgs& a, const int32_t (&it)[kItemInts], u32x4* 
       if (gw >= 0 && gw < n_groups) {
 #pragma unroll
         for (int t = 0; t < TPBF; ++t)
-          if (gw * TPBF + t < n_chunks)
+          if (t % RG == rgi && gw * TPBF + t < n_chunks)
             chunk(gw * TPBF + t, (TPBF * (PWAVE ? u : u + NGS - 1) + t) % NSTF);
       }
     }
   }
 
+  // quad i of the key: 4 dims at (i >> 2) * 32 + (i & 3) * 8 + hh * 4; the row
+  // groups share out the quads of a key, each summed in group order
+  constexpr int NQ = D / 8, NQW = NQ / RG;
+  float sum[NQW][4];
+  if constexpr (RG == 1) {
+#pragma unroll
+    for (int i = 0; i < NQW; ++i)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) sum[i][x] = acc[i >> 2][(i & 3) * 4 + x];
+  } else {
+    static_assert(S::SMEM >= 2 * NPF * NQ * 64, "exchange fits the stages");
+    __syncthreads();  // (every copy has landed: the last group's barrier waited for it)
+    f32x4* xs = (f32x4*)smem;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i)
+      xs[(w * NQ + i) * 64 + lane] = f32x4{acc[i >> 2][(i & 3) * 4], acc[i >> 2][(i & 3) * 4 + 1],
+                                           acc[i >> 2][(i & 3) * 4 + 2], acc[i >> 2][(i & 3) * 4 + 3]};
+    __syncthreads();
+    const int w0 = w - rgi * (NPF / RG);  // the pair's wavefront of row group 0
+#pragma unroll
+    for (int i = 0; i < NQW; ++i) {
+#pragma unroll
+      for (int p = 0; p < RG; ++p) {
+        const f32x4 v = xs[((w0 + p * (NPF / RG)) * NQ + rgi * NQW + i) * 64 + lane];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) sum[i][x] = p ? sum[i][x] + v[x] : v[x];
+      }
+    }
+  }
   if (!key_ok) return;
   const float sc = PWAVE ? 1.f : a.scale;
 #pragma unroll
-  for (int d = 0; d < DB; ++d)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int dim = d * 32 + j * 8 + hh * 4;
-      const float x0 = acc[d][j * 4] * sc, x1 = acc[d][j * 4 + 1] * sc;
-      const float x2 = acc[d][j * 4 + 2] * sc, x3 = acc[d][j * 4 + 3] * sc;
-      if (a.direct) {
-        const int64_t o = ((int64_t)key * a.Hkv + kvh) * D + dim;
-        *(u32x2*)((PWAVE ? a.dv : a.dk) + o) = pack_bf16x4(x0, x1, x2, x3);
-      } else {
-        const int64_t o = ((int64_t)head * a.T_k + key) * D + dim;
-        *(float4*)((PWAVE ? a.part_v : a.part_k) + o) = make_float4(x0, x1, x2, x3);
-      }
+  for (int i = 0; i < NQW; ++i) {
+    const int qi = rgi * NQW + i;
+    const int dim = (qi >> 2) * 32 + (qi & 3) * 8 + hh * 4;
+    const float x0 = sum[i][0] * sc, x1 = sum[i][1] * sc;
+    const float x2 = sum[i][2] * sc, x3 = sum[i][3] * sc;
+    if (a.direct) {
+      const int64_t o = ((int64_t)key * a.Hkv + kvh) * D + dim;
+      *(u32x2*)((PWAVE ? a.dv : a.dk) + o) = pack_bf16x4(x0, x1, x2, x3);
+    } else {
+      const int64_t o = ((int64_t)head * a.T_k + key) * D + dim;
+      *(float4*)((PWAVE ? a.part_v : a.part_k) + o) = make_float4(x0, x1, x2, x3);
     }
+  }
 }
 
-template <int D>
+template <int D, int RG>
 __global__ __launch_bounds__(64 * 2 * NPF, 1) void attn_dkdv_kernel(DkdvArgs a) {
   __shared__ u32x4 smem[DkdvStage<D>::SMEM];
   int32_t it[kItemInts];
-  load_item(a.items, blockIdx.x, it);
+  int pos = blockIdx.x, sub = 0;
+  if constexpr (RG > 1)
+    if (!split_pos<RG>(a.n_items, pos, sub)) return;
+  load_item(a.items, pos, it);
+  if constexpr (RG > 1) {
+    // (the first keys, which a causal mask shows to the most rows, first)
+    if (!split_rows<RG>(it[7] == kItemFillKV, 32 * NPF / RG, RG - 1 - sub, it[0], it[1])) return;
+    if (a.causal) it[2] = max(it[2], it[0] - it[4]);
+  }
   if (it[7] == kItemFillKV) {  // KV head no real query head reads: dK = dV = +0
     fill_rows_bf16(a.dk, it[0], it[1], a.Hkv, it[6], D, threadIdx.x, 64 * 2 * NPF);
     fill_rows_bf16(a.dv, it[0], it[1], a.Hkv, it[6], D, threadIdx.x, 64 * 2 * NPF);
@@ -515,24 +601,37 @@ __global__ __launch_bounds__(64 * 2 * NPF, 1) void attn_dkdv_kernel(DkdvArgs a) 
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (w < NPF)
-    dkdv_body<D, true>(a, it, smem, w, lane);
+    dkdv_body<D, true, RG>(a, it, smem, w, lane);
   else
-    dkdv_body<D, false>(a, it, smem, w, lane);
+    dkdv_body<D, false, RG>(a, it, smem, w, lane);
 }
 
 }  // namespace
 
-hipError_t launch_attn_dq(const DqArgs& a, int n_items, int D, hipStream_t st) {
-  if (n_items <= 0) return hipSuccess;
-  if (D == 128) return sp_launch(kKDq, attn_dq_kernel<128>, dim3(n_items), dim3(NTQ), st, a);
-  return sp_launch(kKDq, attn_dq_kernel<64>, dim3(n_items), dim3(NTQ), st, a);
+template <int KW>
+static hipError_t launch_dq(const DqArgs& a, int D, hipStream_t st) {
+  const dim3 grid(split_grid(a.n_items, KW)), block(NTQ);
+  if (D == 128) return sp_launch(kKDq, attn_dq_kernel<128, KW>, grid, block, st, a);
+  return sp_launch(kKDq, attn_dq_kernel<64, KW>, grid, block, st, a);
 }
 
-hipError_t launch_attn_dkdv(const DkdvArgs& a, int n_items, int D, hipStream_t st) {
-  if (n_items <= 0) return hipSuccess;
-  const dim3 g(n_items), b(64 * 2 * NPF);
-  if (D == 128) return sp_launch(kKDkdv, attn_dkdv_kernel<128>, g, b, st, a);
-  return sp_launch(kKDkdv, attn_dkdv_kernel<64>, g, b, st, a);
+hipError_t launch_attn_dq(const DqArgs& a, int split, int D, hipStream_t st) {
+  if (a.n_items <= 0) return hipSuccess;
+  if (split == 4) return launch_dq<4>(a, D, st);
+  if (split == 2) return launch_dq<2>(a, D, st);
+  return launch_dq<1>(a, D, st);
+}
+
+template <int RG>
+static hipError_t launch_dkdv(const DkdvArgs& a, int D, hipStream_t st) {
+  const dim3 g(split_grid(a.n_items, RG)), b(64 * 2 * NPF);
+  if (D == 128) return sp_launch(kKDkdv, attn_dkdv_kernel<128, RG>, g, b, st, a);
+  return sp_launch(kKDkdv, attn_dkdv_kernel<64, RG>, g, b, st, a);
+}
+
+hipError_t launch_attn_dkdv(const DkdvArgs& a, int split, int D, hipStream_t st) {
+  if (a.n_items <= 0) return hipSuccess;
+  return split == 2 ? launch_dkdv<2>(a, D, st) : launch_dkdv<1>(a, D, st);
 }
 
 }  // namespace spk

@@ -88,21 +88,14 @@ __global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a) {
   __shared__ u32x4 smem[S::SMEM];
 
   int pos = blockIdx.x, sub = 0;
-  if constexpr (KW > 1) {
-    const int j = blockIdx.x >> 3;  // the XCD's j-th workgroup
-    pos = (j / KW) * 8 + (blockIdx.x & 7);
-    sub = KW - 1 - j % KW;
-    if (pos >= a.n_items) return;
-  }
+  if constexpr (KW > 1)
+    if (!split_pos<KW>(a.n_items, pos, sub)) return;
   const int32_t* it = a.items + (int64_t)pos * kItemInts;
   int q0 = it[0], q1 = it[1], k1 = it[3];
   const int k0 = it[2], delta = it[4], head = it[5], kvh = it[6];
   const int tid = threadIdx.x;
   if constexpr (KW > 1) {
-    const int rows = it[7] == kItemFillQ ? (q1 - q0 + KW - 1) / KW : 32 * RW;
-    q0 += sub * rows;
-    q1 = min(q1, q0 + rows);
-    if (q0 >= q1) return;
+    if (!split_rows<KW>(it[7] == kItemFillQ, 32 * RW, sub, q0, q1)) return;
     if (a.causal) k1 = max(k0, min(k1, q1 + delta));
   }
   if (it[7] == kItemFillQ) {
@@ -429,8 +422,7 @@ __global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a) {
 
 template <int KW>
 static hipError_t launch_fwd(const FwdArgs& a, int D, bool merge, hipStream_t st) {
-  // KW workgroups an item, eight items (one an XCD) at a time
-  const dim3 grid(KW == 1 ? a.n_items : (a.n_items + 7) / 8 * 8 * KW), block(NT);
+  const dim3 grid(split_grid(a.n_items, KW)), block(NT);
   if (D == 128)
     return merge ? sp_launch(kKFwd, attn_fwd_kernel<128, true, KW>, grid, block, st, a)
                  : sp_launch(kKFwd, attn_fwd_kernel<128, false, KW>, grid, block, st, a);

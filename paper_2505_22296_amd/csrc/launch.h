@@ -116,6 +116,7 @@ struct DqArgs {
   int T_q, T_k, H, Hkv;
   float scale_log2, scale;
   int causal;
+  int n_items;
 };
 
 struct DkdvArgs {
@@ -133,7 +134,13 @@ struct DkdvArgs {
   int T_q, T_k, H, Hkv;
   float scale_log2, scale;
   int causal, direct;
+  int n_items;
 };
+
+// Workgroups of a launch that splits each of n items over `split` of them.
+static inline unsigned split_grid(int n, int split) {
+  return split == 1 ? n : (unsigned)(n + 7) / 8 * 8 * split;
+}
 
 hipError_t launch_pack(const void* src, void* dst, const PackArgs& a, hipStream_t st);
 hipError_t launch_unpack(const void* src, void* dst, const PackArgs& a, hipStream_t st);
@@ -158,8 +165,8 @@ hipError_t launch_reduce_kv(const float* part_k, const float* part_v, void* dk, 
 
 // `split` workgroups an item (1, 2 or 4): 256 / split rows each
 hipError_t launch_attn_fwd(const FwdArgs& a, int split, int D, bool merge, hipStream_t st);
-hipError_t launch_attn_dq(const DqArgs& a, int n_items, int D, hipStream_t st);
-hipError_t launch_attn_dkdv(const DkdvArgs& a, int n_items, int D, hipStream_t st);
+hipError_t launch_attn_dq(const DqArgs& a, int split, int D, hipStream_t st);
+hipError_t launch_attn_dkdv(const DkdvArgs& a, int split, int D, hipStream_t st);
 
 // Tile sizes the host scheduler must use (rows per fwd/dq item, keys per
 // dk/dv item) and the kernels' LDS pipelines.
