@@ -272,48 +272,113 @@ void sort_items(std::vector<Item>& items, std::vector<int32_t>& out, size_t n_fr
 // Workgroups an item is split over, for launches whose items would leave CUs
 // idle.  With S workgroups an item, each owns 1 / S of its rows (keys) and its
 // wavefronts form S groups that walk the keys (rows) side by side: 1 / S of
-// the steps, but every staged tile serves 1 / S of the rows.  Modelled in
-// steps of an unsplit workgroup: `rel[i]`, a step's cost at S = 2^i against
-// one at S = 1 (28 heads of 4096 rows at D = 128, every CU busy: forward 122,
-// 150, 193 us; dQ 163, 190, 234; dK/dV 229, 280), and `start`, what a
-// workgroup's start and end cost (about 6 us).  A launch takes at least the
-// average load of the 256 CUs and, for each k, k + 1 times its (256 k)-th
-// longest workgroup (of the first 256 k + 1, k + 1 share a CU); the S with the
-// lowest such bound is taken.  The largest items of small launches decide:
-// 4 heads of 4096 rows take S = 4 in the forward (92 -> 43 us), 28 heads of
-// 4096 rows stay whole.  `sorted`: longest first.
+// the steps, but every staged tile serves 1 / S of the rows.  The model, in
+// microseconds: `step`, an unsplit workgroup's step where half the CUs idle;
+// `rel[i]`, a step's cost at S = 2^i against one at S = 1 (28 heads of 4096
+// rows at D = 128, every CU busy: forward 122, 150, 193 us; dQ 163, 190, 234;
+// dK/dV 229, 280); kStartUs, a workgroup's start and end.  A launch takes at
+// least the average load of the 256 CUs and, for each k, k + 1 times its
+// (256 k)-th longest workgroup (of the first 256 k + 1, k + 1 share a CU); the
+// S with the lowest such bound is taken.  The largest items of small launches
+// decide: 4 heads of 4096 rows take S = 4 in the forward (92 -> 43 us), 28
+// heads of 4096 rows stay whole.
 struct SplitModel {
   int n;  // S = 1, 2, .. 2^(n-1)
-  double start, rel[3];
+  double step, rel[3];
 };
-constexpr SplitModel kSplitFwd{3, 4, {1.0, 1.22, 1.6}};   // steps of 64 keys
-constexpr SplitModel kSplitDq{3, 8, {1.0, 1.15, 1.45}};   // steps of 32 keys
-constexpr SplitModel kSplitDkdv{2, 8, {1.0, 1.22, 0}};    // steps of 32 rows
+constexpr double kStartUs = 8;
+constexpr size_t kCus = 256;
+constexpr SplitModel kSplitFwd{3, 2.0, {1.0, 1.22, 1.6}};    // steps of 64 keys
+constexpr SplitModel kSplitDq{3, 1.03, {1.0, 1.15, 1.45}};   // steps of 32 keys
+constexpr SplitModel kSplitDkdv{2, 0.72, {1.0, 1.22, 0}};    // steps of 32 rows
 
-int choose_split(const std::vector<Item>& sorted, const SplitModel& m) {
-  constexpr size_t kCus = 256;
-  double total = 0;
-  for (const Item& it : sorted) total += (double)it.cost;
-  const size_t N = sorted.size();
-  int best = 1;
-  double best_t = 0;
-  for (int i = 0; i < m.n; ++i) {
-    const int S = 1 << i;
-    double t = (total * m.rel[i] + (double)(N * S) * m.start) / kCus;
-    for (size_t k = 0; k * kCus < N * S; ++k)
-      t = std::max(t, (double)(k + 1) *
-                          ((double)sorted[k * kCus / S].cost / S * m.rel[i] + m.start));
-    if (i == 0 || t < best_t) {
-      best = S;
-      best_t = t;
-    }
+// The workgroups of one work list split S = 2^i ways: `cost` holds the items'
+// steps, longest first.
+struct WgList {
+  const std::vector<int>& cost;
+  const SplitModel& m;
+  int i;
+  size_t size() const { return cost.size() << i; }
+  double us(size_t w) const {  // of the w-th longest
+    return (double)cost[w >> i] / (1 << i) * m.rel[i] * m.step + kStartUs;
   }
-  return best;
+};
+
+// Lower bound of a launch of up to two lists.
+double launch_bound(const WgList* lists, int n) {
+  double total = 0, t = 0;
+  size_t at[2] = {0, 0};
+  for (size_t w = 0;; ++w) {
+    int l = -1;
+    for (int x = 0; x < n; ++x)
+      if (at[x] < lists[x].size() && (l < 0 || lists[x].us(at[x]) > lists[l].us(at[l]))) l = x;
+    if (l < 0) break;
+    const double us = lists[l].us(at[l]++);
+    total += us;
+    if (w % kCus == 0) t = std::max(t, (double)(w / kCus + 1) * us);
+  }
+  return std::max(t, total / kCus);
 }
 
-// Row-tile items (forward, ring step, dQ).  Returns the split of the launch.
-int schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN, const SplitModel& m,
-                  bool include_empty, std::vector<int32_t>& out, size_t n_front) {
+// Items past which nothing is split or put into one launch: 16 rounds of 256
+// workgroups, whose end costs a few percent at most.
+constexpr size_t kSplitItems = 4096;
+
+// log2 of the split, and the bound of the launch.
+int choose_split(const std::vector<int>& cost, const SplitModel& m, double& best) {
+  int b = 0;
+  best = 0;
+  if (cost.size() > kSplitItems) return 0;
+  for (int i = 0; i < m.n; ++i) {
+    const WgList l{cost, m, i};
+    const double t = launch_bound(&l, 1);
+    if (i == 0 || t < best) {
+      b = i;
+      best = t;
+    }
+  }
+  return b;
+}
+
+// How a backward call runs its two work lists: one after the other, each with
+// the split it would take alone, or in one launch (the list with the longer
+// workgroups first), where the second list fills the CUs that the first leaves
+// idle at its end.  One launch is taken where the model sees at least 4% in it:
+// 4 heads of 1024 rows 48 -> 31 us a call, 14 heads of 2734 rows without a mask
+// 247 -> 205, 12289 rows in segments of about 700 162 -> 143; a ring chunk of
+// 16384 rows, whose lists fill every round, is 1% slower that way.
+struct BwdPlan {
+  int split_q, split_k;
+  bool one, dq_first;
+};
+BwdPlan plan_bwd(const std::vector<int>& cq, const std::vector<int>& ck) {
+  double tq = 0, tk = 0;
+  const int iq = choose_split(cq, kSplitDq, tq), ik = choose_split(ck, kSplitDkdv, tk);
+  BwdPlan p{1 << iq, 1 << ik, false, false};
+  if (cq.empty() || ck.empty() || cq.size() + ck.size() > kSplitItems) return p;
+  constexpr double kLaunchUs = 4;
+  double best = (tq + tk + kLaunchUs) / 1.04;
+  constexpr int kPairs[3][2] = {{0, 0}, {1, 0}, {2, 1}};
+  for (const auto& s : kPairs) {
+    const WgList l[2] = {{cq, kSplitDq, s[0]}, {ck, kSplitDkdv, s[1]}};
+    const double t = launch_bound(l, 2);
+    if (t < best) {
+      best = t;
+      p = BwdPlan{1 << s[0], 1 << s[1], true, l[0].us(0) > l[1].us(0)};
+    }
+  }
+  return p;
+}
+
+std::vector<int> costs_of(const std::vector<Item>& sorted) {
+  std::vector<int> c(sorted.size());
+  for (size_t i = 0; i < c.size(); ++i) c[i] = (int)sorted[i].cost;
+  return c;
+}
+
+// Row-tile items (forward, ring step, dQ).  Returns their steps, longest first.
+std::vector<int> schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN,
+                               bool include_empty, std::vector<int32_t>& out, size_t n_front) {
   std::vector<Item> items;
   for (int y = 0; y < p.n_real; ++y) {
     for (const Seg& g : p.segs) {
@@ -340,13 +405,13 @@ int schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN, const
         items.push_back(Item{{a, std::min(a + BM, d->T_q), 0, 0, 0, y, p.kv_of[y], 0}, 0});
   }
   sort_items(items, out, n_front, true);  // (leaves `items` longest first)
-  return choose_split(items, m);
+  return costs_of(items);
 }
 
 // Key-tile items (dK / dV).  Every key of every real head gets exactly one
-// item.  Returns the split of the launch.
-int schedule_keys(const sp_attn_desc* d, const Problem& p, int BNK, int BQ,
-                  std::vector<int32_t>& out, size_t n_front) {
+// item.  Returns their steps, longest first.
+std::vector<int> schedule_keys(const sp_attn_desc* d, const Problem& p, int BNK, int BQ,
+                               std::vector<int32_t>& out, size_t n_front) {
   std::vector<Item> items;
   for (int y = 0; y < p.n_real; ++y) {
     for (const Seg& g : p.segs_k) {
@@ -364,7 +429,7 @@ int schedule_keys(const sp_attn_desc* d, const Problem& p, int BNK, int BQ,
       items.push_back(Item{{a, std::min(a + BNK, d->T_k), 0, 0, 0, y, p.kv_of[y], 1}, 0});
   }
   sort_items(items, out, n_front, false);
-  return choose_split(items, kSplitDkdv);
+  return costs_of(items);
 }
 
 // Zero fills as work items of the same launch (no extra kernels): dummy
@@ -695,7 +760,7 @@ sp_status sp_attn_schedule(const sp_attn_desc* desc, int32_t op, int32_t* items,
   // in launch order: the fill items that precede the listed ones there
   // shift the workgroup -> XCD map
   if (op == SP_OP_FWD || op == SP_OP_RING_STEP)
-    schedule_rows(desc, p, spk::kFwdBM, spk::kFwdBN, kSplitFwd, true, v,
+    schedule_rows(desc, p, spk::kFwdBM, spk::kFwdBN, true, v,
                   row_fills(desc, p).size() / kItemInts);
   else if (op == SP_OP_BWD)
     schedule_keys(desc, p, spk::kDkdvBN, spk::kDkdvBQ, v, key_fills(desc, p).size() / kItemInts);
@@ -777,8 +842,8 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
   const bool include_empty = !ring || init || o_out;
   std::vector<int32_t> items;
   const std::vector<int32_t> fills = include_empty ? row_fills(d, p) : std::vector<int32_t>();
-  const int split = schedule_rows(d, p, spk::kFwdBM, spk::kFwdBN, kSplitFwd, include_empty,
-                                  items, fills.size() / kItemInts);
+  const std::vector<int> cost = schedule_rows(d, p, spk::kFwdBM, spk::kFwdBN, include_empty,
+                                              items, fills.size() / kItemInts);
   prepend(fills, items);
   const int n_items = (int)(items.size() / kItemInts);
   hipStream_t st = (hipStream_t)stream;
@@ -812,7 +877,8 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
     a.causal = d->causal;
     a.init = init;
     a.n_items = n_items;
-    SP_HIP(spk::launch_attn_fwd(a, split, p.D, ring, st));
+    double us;
+    SP_HIP(spk::launch_attn_fwd(a, 1 << choose_split(cost, kSplitFwd, us), p.D, ring, st));
   }
   return SP_OK;
 }
@@ -861,10 +927,10 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
   // a dq_acc's dummy slots stay untouched
   const std::vector<int32_t> fq = dq ? row_fills(d, p) : std::vector<int32_t>();
   const std::vector<int32_t> fkv = key_fills(d, p);
-  const int split_q =
-      schedule_rows(d, p, spk::kDqBM, spk::kDqBN, kSplitDq, true, it_dq, fq.size() / kItemInts);
+  const std::vector<int> cost_q =
+      schedule_rows(d, p, spk::kDqBM, spk::kDqBN, true, it_dq, fq.size() / kItemInts);
   prepend(fq, it_dq);
-  const int split_k =
+  const std::vector<int> cost_k =
       schedule_keys(d, p, spk::kDkdvBN, spk::kDkdvBQ, it_kv, fkv.size() / kItemInts);
   prepend(fkv, it_kv);
   const size_t na = it_dq.size() / kItemInts, nb = it_kv.size() / kItemInts;
@@ -897,7 +963,6 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     a.T_q = d->T_q; a.T_k = d->T_k; a.H = d->H_loc; a.Hkv = d->Hkv_loc;
     a.scale_log2 = sl2; a.scale = d->softmax_scale; a.causal = d->causal;
     a.n_items = (int)na;
-    SP_HIP(spk::launch_attn_dq(a, split_q, D, st));
 
     spk::DkdvArgs b{};
     b.q = (const uint16_t*)q;
@@ -910,7 +975,13 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     b.T_q = d->T_q; b.T_k = d->T_k; b.H = d->H_loc; b.Hkv = d->Hkv_loc;
     b.scale_log2 = sl2; b.scale = d->softmax_scale; b.causal = d->causal; b.direct = p.direct;
     b.n_items = (int)nb;
-    SP_HIP(spk::launch_attn_dkdv(b, split_k, D, st));
+    const BwdPlan plan = plan_bwd(cost_q, cost_k);
+    if (plan.one) {
+      SP_HIP(spk::launch_attn_bwd(a, b, plan.split_q, plan.split_k, plan.dq_first, D, st));
+    } else {
+      SP_HIP(spk::launch_attn_dq(a, plan.split_q, D, st));
+      SP_HIP(spk::launch_attn_dkdv(b, plan.split_k, D, st));
+    }
     if (!p.direct && p.n_real > 0) {
       spk::ReduceArgs r{};
       r.T = d->T_k; r.Hkv = d->Hkv_loc; r.D = D;

@@ -214,9 +214,9 @@ SP_DEV void load_item(const int32_t* items, int64_t pos, int32_t (&v)[8]) {
 // keys).  The grid holds S workgroups for every position, rounded up to eight
 // positions (split_grid); false past the list.
 template <int S>
-SP_DEV bool split_pos(int n_items, int& pos, int& sub) {
-  const int j = blockIdx.x >> 3;  // the XCD's j-th workgroup
-  pos = (j / S) * 8 + (blockIdx.x & 7);
+SP_DEV bool split_pos(int block, int n_items, int& pos, int& sub) {
+  const int j = block >> 3;  // the XCD's j-th workgroup
+  pos = S > 1 ? (j / S) * 8 + (block & 7) : block;
   sub = S - 1 - j % S;
   return pos < n_items;
 }

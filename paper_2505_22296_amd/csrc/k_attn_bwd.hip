@@ -62,18 +62,17 @@ struct DqStage {
   static constexpr int SMEM = NST * STAGE > XCH ? NST * STAGE : XCH;
 };
 
+// `block`: the workgroup's number among the launch's dQ workgroups.
 template <int D, int KW>
-__global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
+SP_DEV void dq_body(const DqArgs& a, u32x4* smem, int block) {
   using S = DqStage<D, KW>;
   constexpr int RW = S::RW, BN = S::BN, KS = D / 16, DB = D / 32, NST = S::NST, TPB = S::TPB;
   constexpr int NBW = S::NBW, STAGE = S::STAGE, SUB = S::SUB;
 
-  __shared__ u32x4 smem[S::SMEM];
-
-  int pos = blockIdx.x, sub = 0;
-  if constexpr (KW > 1)
-    if (!split_pos<KW>(a.n_items, pos, sub)) return;
-  const int32_t* it = a.items + (int64_t)pos * kItemInts;
+  int pos, sub;
+  if (!split_pos<KW>(block, a.n_items, pos, sub)) return;
+  int32_t it[kItemInts];
+  load_item(a.items, pos, it);
   int q0 = it[0], q1 = it[1], k1 = it[3];
   const int k0 = it[2], delta = it[4], head = it[5], kvh = it[6];
   const int tid = threadIdx.x;
@@ -297,6 +296,12 @@ __global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
       *(u32x2*)(a.dq + base + dim(i)) =
           pack_bf16x4(sum[i][0] * sc, sum[i][1] * sc, sum[i][2] * sc, sum[i][3] * sc);
   }
+}
+
+template <int D, int KW>
+__global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
+  __shared__ u32x4 smem[DqStage<D, KW>::SMEM];
+  dq_body<D, KW>(a, smem, blockIdx.x);
 }
 
 // ---------------------------------------------------------------- dK / dV
@@ -580,13 +585,12 @@ SP_DEV void dkdv_body(const DkdvArgs& a, const int32_t (&it)[kItemInts], u32x4* 
   }
 }
 
+// `block`: the workgroup's number among the launch's dK/dV workgroups.
 template <int D, int RG>
-__global__ __launch_bounds__(64 * 2 * NPF, 1) void attn_dkdv_kernel(DkdvArgs a) {
-  __shared__ u32x4 smem[DkdvStage<D>::SMEM];
+SP_DEV void dkdv_wg(const DkdvArgs& a, u32x4* smem, int block) {
   int32_t it[kItemInts];
-  int pos = blockIdx.x, sub = 0;
-  if constexpr (RG > 1)
-    if (!split_pos<RG>(a.n_items, pos, sub)) return;
+  int pos, sub;
+  if (!split_pos<RG>(block, a.n_items, pos, sub)) return;
   load_item(a.items, pos, it);
   if constexpr (RG > 1) {
     // (the first keys, which a causal mask shows to the most rows, first)
@@ -604,6 +608,35 @@ __global__ __launch_bounds__(64 * 2 * NPF, 1) void attn_dkdv_kernel(DkdvArgs a) 
     dkdv_body<D, true, RG>(a, it, smem, w, lane);
   else
     dkdv_body<D, false, RG>(a, it, smem, w, lane);
+}
+
+template <int D, int RG>
+__global__ __launch_bounds__(64 * 2 * NPF, 1) void attn_dkdv_kernel(DkdvArgs a) {
+  __shared__ u32x4 smem[DkdvStage<D>::SMEM];
+  dkdv_wg<D, RG>(a, smem, blockIdx.x);
+}
+
+// -------------------------------------------------- dQ and dK / dV together
+// Both work lists in one launch, for launches of few workgroups: each alone
+// ends with most CUs idle behind its longest items (or a last round that
+// fills few CUs); together the second list's workgroups fill the first's
+// tail (backward calls of 4 heads, D = 128: 1024 rows 48 -> 31 us, 4096 rows
+// 125 -> 99; 14 heads of 2734 rows without a mask 247 -> 205).  Workgroups
+// [0, n_first) run the list with the longer workgroups: 28 heads of 2048 rows
+// 148 us with dQ, whose items are the longer ones there, first, 160 us last.
+template <int D, int KW, int RG>
+__global__ __launch_bounds__(NTQ, 1) void attn_bwd_kernel(DqArgs a, DkdvArgs b, int n_first,
+                                                          int dq_first) {
+  static_assert(NTQ == 64 * 2 * NPF, "one workgroup size");
+  using Q = DqStage<D, KW>;
+  using K = DkdvStage<D>;
+  __shared__ u32x4 smem[Q::SMEM > K::SMEM ? Q::SMEM : K::SMEM];
+  const bool first = (int)blockIdx.x < n_first;
+  const int block = first ? blockIdx.x : blockIdx.x - n_first;
+  if (first == (dq_first != 0))
+    dq_body<D, KW>(a, smem, block);
+  else
+    dkdv_wg<D, RG>(b, smem, block);
 }
 
 }  // namespace
@@ -632,6 +665,29 @@ static hipError_t launch_dkdv(const DkdvArgs& a, int D, hipStream_t st) {
 hipError_t launch_attn_dkdv(const DkdvArgs& a, int split, int D, hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
   return split == 2 ? launch_dkdv<2>(a, D, st) : launch_dkdv<1>(a, D, st);
+}
+
+template <int KW, int RG>
+static hipError_t launch_bwd(const DqArgs& a, const DkdvArgs& b, bool dq_first, int D,
+                             hipStream_t st) {
+  // the first list's workgroups are rounded up to eight, so that the second
+  // list's positions keep their XCDs
+  const int nq = split_grid(a.n_items, KW), nk = split_grid(b.n_items, RG);
+  const int n_first = ((dq_first ? nq : nk) + 7) / 8 * 8;
+  const dim3 grid(n_first + (dq_first ? nk : nq)), block(NTQ);
+  if (D == 128)
+    return sp_launch2(kKDq, kKDkdv, attn_bwd_kernel<128, KW, RG>, grid, block, st, a, b, n_first,
+                      (int)dq_first);
+  return sp_launch2(kKDq, kKDkdv, attn_bwd_kernel<64, KW, RG>, grid, block, st, a, b, n_first,
+                    (int)dq_first);
+}
+
+hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, int split_q, int split_k,
+                           bool dq_first, int D, hipStream_t st) {
+  if (split_q == 4 && split_k == 2) return launch_bwd<4, 2>(a, b, dq_first, D, st);
+  if (split_q == 2 && split_k == 1) return launch_bwd<2, 1>(a, b, dq_first, D, st);
+  if (split_q == 1 && split_k == 1) return launch_bwd<1, 1>(a, b, dq_first, D, st);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace spk

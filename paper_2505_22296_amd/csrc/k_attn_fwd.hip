@@ -87,9 +87,8 @@ __global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a) {
 
   __shared__ u32x4 smem[S::SMEM];
 
-  int pos = blockIdx.x, sub = 0;
-  if constexpr (KW > 1)
-    if (!split_pos<KW>(a.n_items, pos, sub)) return;
+  int pos, sub;
+  if (!split_pos<KW>(blockIdx.x, a.n_items, pos, sub)) return;
   const int32_t* it = a.items + (int64_t)pos * kItemInts;
   int q0 = it[0], q1 = it[1], k1 = it[3];
   const int k0 = it[2], delta = it[4], head = it[5], kvh = it[6];

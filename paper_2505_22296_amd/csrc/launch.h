@@ -37,6 +37,23 @@ inline hipError_t sp_launch(int id, F kernel, dim3 grid, dim3 block, hipStream_t
   return e;
 }
 
+// The same for a launch that does the work of two kernels: both timers
+// describe it.
+template <typename F, typename... Args>
+inline hipError_t sp_launch2(int id_a, int id_b, F kernel, dim3 grid, dim3 block, hipStream_t st,
+                             Args... args) {
+  KernelTimer &ta = timer_for(id_a), &tb = timer_for(id_b);
+  hipError_t e = hipSuccess;
+  if (ta.start) e = hipEventRecord(ta.start, st);
+  if (e == hipSuccess && tb.start) e = hipEventRecord(tb.start, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, grid, block, 0, st, args...);
+  e = hipGetLastError();
+  if (e == hipSuccess && ta.stop) e = hipEventRecord(ta.stop, st);
+  if (e == hipSuccess && tb.stop) e = hipEventRecord(tb.stop, st);
+  return e;
+}
+
 // Maximum head-map entries a pack/unpack carries by value in its arguments.
 static constexpr int kMaxMap = 512;
 // Maximum local KV heads for the GQA dK/dV reduction.
@@ -167,6 +184,10 @@ hipError_t launch_reduce_kv(const float* part_k, const float* part_v, void* dk, 
 hipError_t launch_attn_fwd(const FwdArgs& a, int split, int D, bool merge, hipStream_t st);
 hipError_t launch_attn_dq(const DqArgs& a, int split, int D, hipStream_t st);
 hipError_t launch_attn_dkdv(const DkdvArgs& a, int split, int D, hipStream_t st);
+// dQ and dK/dV in one launch; (split_q, split_k) one of (4, 2), (2, 1),
+// (1, 1).  `dq_first`: the dQ workgroups come first.
+hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, int split_q, int split_k,
+                           bool dq_first, int D, hipStream_t st);
 
 // Tile sizes the host scheduler must use (rows per fwd/dq item, keys per
 // dk/dv item) and the kernels' LDS pipelines.
