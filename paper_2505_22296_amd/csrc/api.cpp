@@ -861,8 +861,14 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
     items_dev = at(ws, L.items_dq);
   }
   if (n_items > 0) {
-    if ((s = upload(items_dev, items, st)) != SP_OK) return s;
     spk::FwdArgs a{};
+    spk::ItemList list;  // (items past the list's are never read)
+    if (n_items <= spk::kInlineItems) {
+      std::copy(items.begin(), items.end(), list.v);
+    } else {
+      if ((s = upload(items_dev, items, st)) != SP_OK) return s;
+      a.items = (const int32_t*)items_dev;
+    }
     a.q = (const uint16_t*)q;
     a.k = (const uint16_t*)k;
     a.v = (const uint16_t*)v;
@@ -871,14 +877,13 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
     a.o_acc = o_acc;
     a.lse_acc = lse_acc;
     a.o_out = (uint16_t*)o_out;
-    a.items = (const int32_t*)items_dev;
     a.T_q = d->T_q; a.T_k = d->T_k; a.H = d->H_loc; a.Hkv = d->Hkv_loc;
     a.scale_log2 = d->softmax_scale * 1.4426950408889634f;
     a.causal = d->causal;
     a.init = init;
     a.n_items = n_items;
     double us;
-    SP_HIP(spk::launch_attn_fwd(a, 1 << choose_split(cost, kSplitFwd, us), p.D, ring, st));
+    SP_HIP(spk::launch_attn_fwd(a, list, 1 << choose_split(cost, kSplitFwd, us), p.D, ring, st));
   }
   return SP_OK;
 }
@@ -940,9 +945,13 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
   if ((s = refuse_capture(st)) != SP_OK) return s;
   const int D = p.D;
   {
-    // both work lists in one copy (they are adjacent in the workspace): every
-    // host-to-device copy sits between two kernels on the stream
-    {
+    // Work lists that fit a launch's arguments go there (a launch of its own
+    // for dK/dV has its list first).  Else both in one copy (they are adjacent
+    // in the workspace): every host-to-device copy sits between two kernels on
+    // the stream.
+    spk::ItemList list;
+    const bool by_value = na + nb <= (size_t)spk::kInlineItems;
+    if (!by_value) {
       const size_t gap = (L.items_kv - L.items_dq) / sizeof(int32_t);
       std::vector<int32_t> both(gap + it_kv.size(), 0);
       std::copy(it_dq.begin(), it_dq.end(), both.begin());
@@ -959,7 +968,7 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     a.dout = (const uint16_t*)dout;
     a.lse = lse; a.neg_d = neg_d; a.dq = (uint16_t*)dq; a.dq_acc = dq_acc;
     a.dq_init = dq_acc && (d->flags & SP_DESC_DQ_ACC_INIT) ? 1 : 0;
-    a.items = (const int32_t*)at(ws, L.items_dq);
+    a.items = by_value ? nullptr : (const int32_t*)at(ws, L.items_dq);
     a.T_q = d->T_q; a.T_k = d->T_k; a.H = d->H_loc; a.Hkv = d->Hkv_loc;
     a.scale_log2 = sl2; a.scale = d->softmax_scale; a.causal = d->causal;
     a.n_items = (int)na;
@@ -971,16 +980,19 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     b.dk = (uint16_t*)dk; b.dv = (uint16_t*)dv;
     b.part_k = p.direct ? nullptr : (float*)at(ws, L.part_k);
     b.part_v = p.direct ? nullptr : (float*)at(ws, L.part_v);
-    b.items = (const int32_t*)at(ws, L.items_kv);
+    b.items = by_value ? nullptr : (const int32_t*)at(ws, L.items_kv);
     b.T_q = d->T_q; b.T_k = d->T_k; b.H = d->H_loc; b.Hkv = d->Hkv_loc;
     b.scale_log2 = sl2; b.scale = d->softmax_scale; b.causal = d->causal; b.direct = p.direct;
     b.n_items = (int)nb;
     const BwdPlan plan = plan_bwd(cost_q, cost_k);
+    if (by_value) std::copy(it_dq.begin(), it_dq.end(), list.v);
     if (plan.one) {
-      SP_HIP(spk::launch_attn_bwd(a, b, plan.split_q, plan.split_k, plan.dq_first, D, st));
+      if (by_value) std::copy(it_kv.begin(), it_kv.end(), list.v + it_dq.size());
+      SP_HIP(spk::launch_attn_bwd(a, b, list, plan.split_q, plan.split_k, plan.dq_first, D, st));
     } else {
-      SP_HIP(spk::launch_attn_dq(a, plan.split_q, D, st));
-      SP_HIP(spk::launch_attn_dkdv(b, plan.split_k, D, st));
+      SP_HIP(spk::launch_attn_dq(a, list, plan.split_q, D, st));
+      if (by_value) std::copy(it_kv.begin(), it_kv.end(), list.v);
+      SP_HIP(spk::launch_attn_dkdv(b, list, plan.split_k, D, st));
     }
     if (!p.direct && p.n_real > 0) {
       spk::ReduceArgs r{};

@@ -207,6 +207,17 @@ SP_DEV void load_item(const int32_t* items, int64_t pos, int32_t (&v)[8]) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) v[j] = p[j];
 }
+// The same from the launch's own list (kernel arguments) where `items` is
+// null; the list's first item is `base` there.
+template <typename List>
+SP_DEV void load_item(const int32_t* items, const List& list, int base, int pos, int32_t (&v)[8]) {
+  if (items) {
+    load_item(items, pos, v);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = list.v[(base + pos) * 8 + j];
+  }
+}
 
 // Launches that split every work item over S workgroups: workgroup b runs on
 // XCD b % 8, and an XCD's S consecutive workgroups share one item of its list

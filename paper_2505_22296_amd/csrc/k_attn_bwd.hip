@@ -64,7 +64,7 @@ struct DqStage {
 
 // `block`: the workgroup's number among the launch's dQ workgroups.
 template <int D, int KW>
-SP_DEV void dq_body(const DqArgs& a, u32x4* smem, int block) {
+SP_DEV void dq_body(const DqArgs& a, const ItemList& list, u32x4* smem, int block) {
   using S = DqStage<D, KW>;
   constexpr int RW = S::RW, BN = S::BN, KS = D / 16, DB = D / 32, NST = S::NST, TPB = S::TPB;
   constexpr int NBW = S::NBW, STAGE = S::STAGE, SUB = S::SUB;
@@ -72,7 +72,7 @@ SP_DEV void dq_body(const DqArgs& a, u32x4* smem, int block) {
   int pos, sub;
   if (!split_pos<KW>(block, a.n_items, pos, sub)) return;
   int32_t it[kItemInts];
-  load_item(a.items, pos, it);
+  load_item(a.items, list, 0, pos, it);
   int q0 = it[0], q1 = it[1], k1 = it[3];
   const int k0 = it[2], delta = it[4], head = it[5], kvh = it[6];
   const int tid = threadIdx.x;
@@ -299,9 +299,9 @@ SP_DEV void dq_body(const DqArgs& a, u32x4* smem, int block) {
 }
 
 template <int D, int KW>
-__global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a) {
+__global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a, ItemList list) {
   __shared__ u32x4 smem[DqStage<D, KW>::SMEM];
-  dq_body<D, KW>(a, smem, blockIdx.x);
+  dq_body<D, KW>(a, list, smem, blockIdx.x);
 }
 
 // ---------------------------------------------------------------- dK / dV
@@ -585,13 +585,14 @@ SP_DEV void dkdv_body(const DkdvArgs& a, const int32_t (&it)[kItemInts], u32x4* 
   }
 }
 
-// `block`: the workgroup's number among the launch's dK/dV workgroups.
+// `block`: the workgroup's number among the launch's dK/dV workgroups; `base`:
+// the first dK/dV item in the list.
 template <int D, int RG>
-SP_DEV void dkdv_wg(const DkdvArgs& a, u32x4* smem, int block) {
+SP_DEV void dkdv_wg(const DkdvArgs& a, const ItemList& list, int base, u32x4* smem, int block) {
   int32_t it[kItemInts];
   int pos, sub;
   if (!split_pos<RG>(block, a.n_items, pos, sub)) return;
-  load_item(a.items, pos, it);
+  load_item(a.items, list, base, pos, it);
   if constexpr (RG > 1) {
     // (the first keys, which a causal mask shows to the most rows, first)
     if (!split_rows<RG>(it[7] == kItemFillKV, 32 * NPF / RG, RG - 1 - sub, it[0], it[1])) return;
@@ -611,9 +612,9 @@ SP_DEV void dkdv_wg(const DkdvArgs& a, u32x4* smem, int block) {
 }
 
 template <int D, int RG>
-__global__ __launch_bounds__(64 * 2 * NPF, 1) void attn_dkdv_kernel(DkdvArgs a) {
+__global__ __launch_bounds__(64 * 2 * NPF, 1) void attn_dkdv_kernel(DkdvArgs a, ItemList list) {
   __shared__ u32x4 smem[DkdvStage<D>::SMEM];
-  dkdv_wg<D, RG>(a, smem, blockIdx.x);
+  dkdv_wg<D, RG>(a, list, 0, smem, blockIdx.x);
 }
 
 // -------------------------------------------------- dQ and dK / dV together
@@ -625,8 +626,8 @@ __global__ __launch_bounds__(64 * 2 * NPF, 1) void attn_dkdv_kernel(DkdvArgs a) 
 // [0, n_first) run the list with the longer workgroups: 28 heads of 2048 rows
 // 148 us with dQ, whose items are the longer ones there, first, 160 us last.
 template <int D, int KW, int RG>
-__global__ __launch_bounds__(NTQ, 1) void attn_bwd_kernel(DqArgs a, DkdvArgs b, int n_first,
-                                                          int dq_first) {
+__global__ __launch_bounds__(NTQ, 1) void attn_bwd_kernel(DqArgs a, DkdvArgs b, ItemList list,
+                                                          int n_first, int dq_first) {
   static_assert(NTQ == 64 * 2 * NPF, "one workgroup size");
   using Q = DqStage<D, KW>;
   using K = DkdvStage<D>;
@@ -634,59 +635,61 @@ __global__ __launch_bounds__(NTQ, 1) void attn_bwd_kernel(DqArgs a, DkdvArgs b, 
   const bool first = (int)blockIdx.x < n_first;
   const int block = first ? blockIdx.x : blockIdx.x - n_first;
   if (first == (dq_first != 0))
-    dq_body<D, KW>(a, smem, block);
+    dq_body<D, KW>(a, list, smem, block);
   else
-    dkdv_wg<D, RG>(b, smem, block);
+    dkdv_wg<D, RG>(b, list, a.n_items, smem, block);
 }
 
 }  // namespace
 
 template <int KW>
-static hipError_t launch_dq(const DqArgs& a, int D, hipStream_t st) {
+static hipError_t launch_dq(const DqArgs& a, const ItemList& list, int D, hipStream_t st) {
   const dim3 grid(split_grid(a.n_items, KW)), block(NTQ);
-  if (D == 128) return sp_launch(kKDq, attn_dq_kernel<128, KW>, grid, block, st, a);
-  return sp_launch(kKDq, attn_dq_kernel<64, KW>, grid, block, st, a);
+  if (D == 128) return sp_launch(kKDq, attn_dq_kernel<128, KW>, grid, block, st, a, list);
+  return sp_launch(kKDq, attn_dq_kernel<64, KW>, grid, block, st, a, list);
 }
 
-hipError_t launch_attn_dq(const DqArgs& a, int split, int D, hipStream_t st) {
+hipError_t launch_attn_dq(const DqArgs& a, const ItemList& list, int split, int D,
+                          hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  if (split == 4) return launch_dq<4>(a, D, st);
-  if (split == 2) return launch_dq<2>(a, D, st);
-  return launch_dq<1>(a, D, st);
+  if (split == 4) return launch_dq<4>(a, list, D, st);
+  if (split == 2) return launch_dq<2>(a, list, D, st);
+  return launch_dq<1>(a, list, D, st);
 }
 
 template <int RG>
-static hipError_t launch_dkdv(const DkdvArgs& a, int D, hipStream_t st) {
+static hipError_t launch_dkdv(const DkdvArgs& a, const ItemList& list, int D, hipStream_t st) {
   const dim3 g(split_grid(a.n_items, RG)), b(64 * 2 * NPF);
-  if (D == 128) return sp_launch(kKDkdv, attn_dkdv_kernel<128, RG>, g, b, st, a);
-  return sp_launch(kKDkdv, attn_dkdv_kernel<64, RG>, g, b, st, a);
+  if (D == 128) return sp_launch(kKDkdv, attn_dkdv_kernel<128, RG>, g, b, st, a, list);
+  return sp_launch(kKDkdv, attn_dkdv_kernel<64, RG>, g, b, st, a, list);
 }
 
-hipError_t launch_attn_dkdv(const DkdvArgs& a, int split, int D, hipStream_t st) {
+hipError_t launch_attn_dkdv(const DkdvArgs& a, const ItemList& list, int split, int D,
+                            hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  return split == 2 ? launch_dkdv<2>(a, D, st) : launch_dkdv<1>(a, D, st);
+  return split == 2 ? launch_dkdv<2>(a, list, D, st) : launch_dkdv<1>(a, list, D, st);
 }
 
 template <int KW, int RG>
-static hipError_t launch_bwd(const DqArgs& a, const DkdvArgs& b, bool dq_first, int D,
-                             hipStream_t st) {
+static hipError_t launch_bwd(const DqArgs& a, const DkdvArgs& b, const ItemList& list,
+                             bool dq_first, int D, hipStream_t st) {
   // the first list's workgroups are rounded up to eight, so that the second
   // list's positions keep their XCDs
   const int nq = split_grid(a.n_items, KW), nk = split_grid(b.n_items, RG);
   const int n_first = ((dq_first ? nq : nk) + 7) / 8 * 8;
   const dim3 grid(n_first + (dq_first ? nk : nq)), block(NTQ);
   if (D == 128)
-    return sp_launch2(kKDq, kKDkdv, attn_bwd_kernel<128, KW, RG>, grid, block, st, a, b, n_first,
-                      (int)dq_first);
-  return sp_launch2(kKDq, kKDkdv, attn_bwd_kernel<64, KW, RG>, grid, block, st, a, b, n_first,
-                    (int)dq_first);
+    return sp_launch2(kKDq, kKDkdv, attn_bwd_kernel<128, KW, RG>, grid, block, st, a, b, list,
+                      n_first, (int)dq_first);
+  return sp_launch2(kKDq, kKDkdv, attn_bwd_kernel<64, KW, RG>, grid, block, st, a, b, list,
+                    n_first, (int)dq_first);
 }
 
-hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, int split_q, int split_k,
-                           bool dq_first, int D, hipStream_t st) {
-  if (split_q == 4 && split_k == 2) return launch_bwd<4, 2>(a, b, dq_first, D, st);
-  if (split_q == 2 && split_k == 1) return launch_bwd<2, 1>(a, b, dq_first, D, st);
-  if (split_q == 1 && split_k == 1) return launch_bwd<1, 1>(a, b, dq_first, D, st);
+hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, const ItemList& list, int split_q,
+                           int split_k, bool dq_first, int D, hipStream_t st) {
+  if (split_q == 4 && split_k == 2) return launch_bwd<4, 2>(a, b, list, dq_first, D, st);
+  if (split_q == 2 && split_k == 1) return launch_bwd<2, 1>(a, b, list, dq_first, D, st);
+  if (split_q == 1 && split_k == 1) return launch_bwd<1, 1>(a, b, list, dq_first, D, st);
   return hipErrorInvalidValue;
 }
 

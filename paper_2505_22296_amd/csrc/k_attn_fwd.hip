@@ -77,7 +77,7 @@ struct FwdStage {
 // over KW workgroups (of 256 / KW rows each), all on the item's XCD, one
 // after the other, the last rows (the longest under a causal mask) first.
 template <int D, bool MERGE, int KW>
-__global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a) {
+__global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a, ItemList list) {
   using S = FwdStage<D, KW>;
   constexpr int RW = S::RW, BN = S::BN, NST = S::NST, TPB = S::TPB;
   constexpr int KS = D / 16;   // MFMA k-steps over D
@@ -89,7 +89,8 @@ __global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a) {
 
   int pos, sub;
   if (!split_pos<KW>(blockIdx.x, a.n_items, pos, sub)) return;
-  const int32_t* it = a.items + (int64_t)pos * kItemInts;
+  int32_t it[kItemInts];
+  load_item(a.items, list, 0, pos, it);
   int q0 = it[0], q1 = it[1], k1 = it[3];
   const int k0 = it[2], delta = it[4], head = it[5], kvh = it[6];
   const int tid = threadIdx.x;
@@ -420,20 +421,22 @@ __global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a) {
 }  // namespace
 
 template <int KW>
-static hipError_t launch_fwd(const FwdArgs& a, int D, bool merge, hipStream_t st) {
+static hipError_t launch_fwd(const FwdArgs& a, const ItemList& list, int D, bool merge,
+                             hipStream_t st) {
   const dim3 grid(split_grid(a.n_items, KW)), block(NT);
   if (D == 128)
-    return merge ? sp_launch(kKFwd, attn_fwd_kernel<128, true, KW>, grid, block, st, a)
-                 : sp_launch(kKFwd, attn_fwd_kernel<128, false, KW>, grid, block, st, a);
-  return merge ? sp_launch(kKFwd, attn_fwd_kernel<64, true, KW>, grid, block, st, a)
-               : sp_launch(kKFwd, attn_fwd_kernel<64, false, KW>, grid, block, st, a);
+    return merge ? sp_launch(kKFwd, attn_fwd_kernel<128, true, KW>, grid, block, st, a, list)
+                 : sp_launch(kKFwd, attn_fwd_kernel<128, false, KW>, grid, block, st, a, list);
+  return merge ? sp_launch(kKFwd, attn_fwd_kernel<64, true, KW>, grid, block, st, a, list)
+               : sp_launch(kKFwd, attn_fwd_kernel<64, false, KW>, grid, block, st, a, list);
 }
 
-hipError_t launch_attn_fwd(const FwdArgs& a, int split, int D, bool merge, hipStream_t st) {
+hipError_t launch_attn_fwd(const FwdArgs& a, const ItemList& list, int split, int D, bool merge,
+                           hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  if (split == 4) return launch_fwd<4>(a, D, merge, st);
-  if (split == 2) return launch_fwd<2>(a, D, merge, st);
-  return launch_fwd<1>(a, D, merge, st);
+  if (split == 4) return launch_fwd<4>(a, list, D, merge, st);
+  if (split == 2) return launch_fwd<2>(a, list, D, merge, st);
+  return launch_fwd<1>(a, list, D, merge, st);
 }
 
 }  // namespace spk

@@ -25,7 +25,7 @@ KernelTimer& timer_for(int kernel_id);
 // used that way.)
 template <typename F, typename... Args>
 inline hipError_t sp_launch(int id, F kernel, dim3 grid, dim3 block, hipStream_t st,
-                            Args... args) {
+                            const Args&... args) {
   KernelTimer& t = timer_for(id);
   if (t.start) {
     hipError_t e = hipEventRecord(t.start, st);
@@ -41,7 +41,7 @@ inline hipError_t sp_launch(int id, F kernel, dim3 grid, dim3 block, hipStream_t
 // describe it.
 template <typename F, typename... Args>
 inline hipError_t sp_launch2(int id_a, int id_b, F kernel, dim3 grid, dim3 block, hipStream_t st,
-                             Args... args) {
+                             const Args&... args) {
   KernelTimer &ta = timer_for(id_a), &tb = timer_for(id_b);
   hipError_t e = hipSuccess;
   if (ta.start) e = hipEventRecord(ta.start, st);
@@ -102,6 +102,17 @@ static constexpr int kItemInts = 8;
 static constexpr int kItemFillQ = 2, kItemFillKV = 3;
 static constexpr int kFillRows = 8192;  // rows (keys) per zero-fill item
 
+// A launch's work list by value in its kernel arguments: lists of up to
+// kInlineItems items (dQ's before dK/dV's where one launch has both) travel
+// with the launch, where `items` is null; longer ones are copied into the
+// workspace.  A copy of 2 / 8 / 16 KB and a launch took 7.0 / 9.6 / 12.7 us,
+// on host and stream alike, a launch with as much in its arguments 3.6 / 3.7 /
+// 3.9 us (one without, 2.6).
+static constexpr int kInlineItems = 512;
+struct ItemList {
+  int32_t v[kInlineItems * kItemInts];
+};
+
 struct FwdArgs {
   const uint16_t* q;   // [T_q, H, D]
   const uint16_t* k;   // [T_k, Hkv, D]
@@ -111,7 +122,7 @@ struct FwdArgs {
   float* o_acc;        // ring: [T_q, H, D] float32 in/out
   float* lse_acc;      // ring: [H, T_q] in/out
   uint16_t* o_out;     // ring: optional bf16 copy of the merged O
-  const int32_t* items;
+  const int32_t* items;  // null: in the launch's ItemList
   int T_q, T_k, H, Hkv;
   float scale_log2;    // softmax_scale * log2(e)
   int causal, init;
@@ -129,7 +140,7 @@ struct DqArgs {
   float* dq_acc;         // float32 [T_q, H, D] or null: with dq, read only
                          // (dq = bf16(dq_acc + dQ)); without, dq_acc += dQ
   int dq_init;           // dq_acc taken as zero (not read)
-  const int32_t* items;
+  const int32_t* items;  // null: in the launch's ItemList
   int T_q, T_k, H, Hkv;
   float scale_log2, scale;
   int causal;
@@ -147,7 +158,7 @@ struct DkdvArgs {
   uint16_t* dv;
   float* part_k;         // float32 [n_real, T_k, D] (GQA partial mode)
   float* part_v;
-  const int32_t* items;
+  const int32_t* items;  // null: in the launch's ItemList
   int T_q, T_k, H, Hkv;
   float scale_log2, scale;
   int causal, direct;
@@ -181,13 +192,13 @@ hipError_t launch_reduce_kv(const float* part_k, const float* part_v, void* dk, 
                             const ReduceArgs& a, hipStream_t st);
 
 // `split` workgroups an item (1, 2 or 4): 256 / split rows each
-hipError_t launch_attn_fwd(const FwdArgs& a, int split, int D, bool merge, hipStream_t st);
-hipError_t launch_attn_dq(const DqArgs& a, int split, int D, hipStream_t st);
-hipError_t launch_attn_dkdv(const DkdvArgs& a, int split, int D, hipStream_t st);
+hipError_t launch_attn_fwd(const FwdArgs& a, const ItemList& list, int split, int D, bool merge, hipStream_t st);
+hipError_t launch_attn_dq(const DqArgs& a, const ItemList& list, int split, int D, hipStream_t st);
+hipError_t launch_attn_dkdv(const DkdvArgs& a, const ItemList& list, int split, int D, hipStream_t st);
 // dQ and dK/dV in one launch; (split_q, split_k) one of (4, 2), (2, 1),
 // (1, 1).  `dq_first`: the dQ workgroups come first.
-hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, int split_q, int split_k,
-                           bool dq_first, int D, hipStream_t st);
+hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, const ItemList& list, int split_q,
+                           int split_k, bool dq_first, int D, hipStream_t st);
 
 // Tile sizes the host scheduler must use (rows per fwd/dq item, keys per
 // dk/dv item) and the kernels' LDS pipelines.
