@@ -7,6 +7,7 @@ compiled library is missing, loading fails loudly: there is no fallback.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import math
 import os
@@ -65,11 +66,12 @@ def load() -> ctypes.CDLL:
     sig = {
         "sp_status_string": (ctypes.c_char_p, [i32]),
         "sp_version": (i32, []),
-        "sp_ulysses_pack": (i32, [vp, i32, i32, i32, i32, i32, _i32p, vp, vp]),
-        "sp_ulysses_unpack": (i32, [vp, i32, i32, i32, i32, _i32p, i32, vp, vp]),
-        "sp_ulysses_unpack_add": (i32, [vp, i32, i32, i32, i32, _i32p, i32, vp, vp]),
-        "sp_token_logprob": (i32, [vp, vp, i32, i32, i32, _i32p, i32, vp, vp, vp, vp]),
-        "sp_token_logprob_bwd": (i32, [vp, vp, vp, i32, i32, i32, _i32p, i32, vp, vp, vp]),
+        # (host int32 arrays as addresses: see _i32)
+        "sp_ulysses_pack": (i32, [vp, i32, i32, i32, i32, i32, vp, vp, vp]),
+        "sp_ulysses_unpack": (i32, [vp, i32, i32, i32, i32, vp, i32, vp, vp]),
+        "sp_ulysses_unpack_add": (i32, [vp, i32, i32, i32, i32, vp, i32, vp, vp]),
+        "sp_token_logprob": (i32, [vp, vp, i32, i32, i32, vp, i32, vp, vp, vp, vp]),
+        "sp_token_logprob_bwd": (i32, [vp, vp, vp, i32, i32, i32, vp, i32, vp, vp, vp]),
         "sp_loss_reduce": (i32, [vp, vp, i32, i32, i32, ctypes.c_float, vp, vp, vp]),
         "sp_attn_workspace_size": (i32, [D, i32, ctypes.POINTER(sz)]),
         "sp_attn_fwd": (i32, [D, vp, vp, vp, vp, vp, vp, sz, vp]),
@@ -156,9 +158,22 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream(stream=None) -> int:
+    """hipStream_t of `stream` or of the current device's current stream (its
+    raw handle: building a Stream object cost 2.7 us of the 9 us of a small
+    call's host time)."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+def _i32(x):
+    """Host int32 array of `x` and its address (valid while the array lives)."""
+    a = np.ascontiguousarray(x, dtype=np.int32)
+    return a, a.__array_interface__["data"][0]
+
+
+_no_context = contextlib.nullcontext()
 
 
 def _alloc_on(stream=None):
@@ -168,10 +183,9 @@ def _alloc_on(stream=None):
     dropped, hands it to the next allocation on that stream without waiting
     for other streams; a workspace allocated on the current stream but read
     by kernels queued on `stream` could be reused while they still run."""
-    import contextlib
-    import torch
     if stream is None:
-        return contextlib.nullcontext()
+        return _no_context
+    import torch
     return torch.cuda.stream(stream)
 
 
@@ -181,12 +195,19 @@ def sp_attn_workspace_size(desc: Desc, op: int) -> int:
     return n.value
 
 
-def _workspace(desc: Desc, op: int, device, ws=None):
+def _with_workspace(desc: Desc, op: int, device, ws, call, where: str):
+    """call(pointer, bytes) with the caller's workspace, or one allocated here
+    if there is none or it is too small.  The library checks the size, so a
+    workspace that fits costs no call of its own (which validates the
+    descriptor, O(T) host work, once more)."""
+    if ws is not None:
+        status = call(ws.data_ptr(), ws.numel())
+        if status != SP_ERR_WORKSPACE or ws.numel() >= sp_attn_workspace_size(desc, op):
+            return _check(status, where)
     import torch
     need = sp_attn_workspace_size(desc, op)
-    if ws is not None and ws.numel() >= need:
-        return ws, ws.numel()
-    return torch.empty(need, dtype=torch.uint8, device=device), need
+    ws = torch.empty(need, dtype=torch.uint8, device=device)
+    _check(call(ws.data_ptr(), need), where)
 
 
 def sp_attn_schedule(desc: Desc, op: int) -> np.ndarray:
@@ -207,9 +228,9 @@ def sp_ulysses_pack(src, sp: int, H_dst_loc: int, head_map: Sequence[int], dst=N
     if dst is None:
         with _alloc_on(stream):
             dst = torch.empty((sp, T, H_dst_loc, D), dtype=src.dtype, device=src.device)
-    m = np.ascontiguousarray(np.asarray(head_map, dtype=np.int32))
-    _check(load().sp_ulysses_pack(_ptr(src), T, Hs, D, sp, H_dst_loc, m.ctypes.data_as(_i32p),
-                                  _ptr(dst), _stream(stream)), "sp_ulysses_pack")
+    m, mp = _i32(head_map)
+    _check(load().sp_ulysses_pack(_ptr(src), T, Hs, D, sp, H_dst_loc, mp, _ptr(dst),
+                                  _stream(stream)), "sp_ulysses_pack")
     return dst
 
 
@@ -220,9 +241,9 @@ def sp_ulysses_unpack(src, head_map: Sequence[int], H_dst: int, dst=None, stream
     if dst is None:
         with _alloc_on(stream):
             dst = torch.empty((T, H_dst, D), dtype=src.dtype, device=src.device)
-    m = np.ascontiguousarray(np.asarray(head_map, dtype=np.int32))
-    _check(load().sp_ulysses_unpack(_ptr(src), T, Hs, D, sp, m.ctypes.data_as(_i32p), H_dst,
-                                    _ptr(dst), _stream(stream)), "sp_ulysses_unpack")
+    m, mp = _i32(head_map)
+    _check(load().sp_ulysses_unpack(_ptr(src), T, Hs, D, sp, mp, H_dst, _ptr(dst),
+                                    _stream(stream)), "sp_ulysses_unpack")
     return dst
 
 
@@ -235,15 +256,15 @@ def sp_ulysses_unpack_add(src, head_map: Sequence[int], H_dst: int, dst=None, st
     if dst is None:
         with _alloc_on(stream):
             dst = torch.empty((T, H_dst, D), dtype=src.dtype, device=src.device)
-    m = np.ascontiguousarray(np.asarray(head_map, dtype=np.int32))
-    _check(load().sp_ulysses_unpack_add(_ptr(src), T, Hs, D, sp, m.ctypes.data_as(_i32p), H_dst,
-                                        _ptr(dst), _stream(stream)), "sp_ulysses_unpack_add")
+    m, mp = _i32(head_map)
+    _check(load().sp_ulysses_unpack_add(_ptr(src), T, Hs, D, sp, mp, H_dst, _ptr(dst),
+                                        _stream(stream)), "sp_ulysses_unpack_add")
     return dst
 
 
 def _cu(cu_seqlens):
-    cu = np.ascontiguousarray(np.asarray(cu_seqlens, dtype=np.int32))
-    return cu, len(cu) - 1
+    cu, p = _i32(cu_seqlens)
+    return cu, p, len(cu) - 1
 
 
 def sp_token_logprob(logits, labels, cu_seqlens, ignore_index: int = -100, logp=None, lse=None,
@@ -252,16 +273,15 @@ def sp_token_logprob(logits, labels, cu_seqlens, ignore_index: int = -100, logp=
     seq_sum [num_seqs]) float32."""
     import torch
     T, V = logits.shape
-    cu, n = _cu(cu_seqlens)
+    cu, cup, n = _cu(cu_seqlens)
     dev = logits.device
     with _alloc_on(stream):
         logp = torch.empty(T, dtype=torch.float32, device=dev) if logp is None else logp
         lse = torch.empty(T, dtype=torch.float32, device=dev) if lse is None else lse
         if seq_sum is None:
             seq_sum = torch.empty(max(n, 0), dtype=torch.float32, device=dev)
-    _check(load().sp_token_logprob(_ptr(logits), _ptr(labels), T, V, ignore_index,
-                                   cu.ctypes.data_as(_i32p), n, _ptr(logp), _ptr(lse),
-                                   _ptr(seq_sum) if n > 0 else None, _stream(stream)),
+    _check(load().sp_token_logprob(_ptr(logits), _ptr(labels), T, V, ignore_index, cup, n,
+                                   _ptr(logp), _ptr(lse), _ptr(seq_sum) if n > 0 else None, _stream(stream)),
            "sp_token_logprob")
     return logp, lse, seq_sum
 
@@ -272,13 +292,13 @@ def sp_token_logprob_bwd(logits, labels, lse, cu_seqlens, grad_seq, ignore_index
     counted token, g = grad_seq[its sequence]."""
     import torch
     T, V = logits.shape
-    cu, n = _cu(cu_seqlens)
+    cu, cup, n = _cu(cu_seqlens)
     if dlogits is None:
         with _alloc_on(stream):
             dlogits = torch.empty_like(logits)
     _check(load().sp_token_logprob_bwd(_ptr(logits), _ptr(labels), _ptr(lse), T, V, ignore_index,
-                                       cu.ctypes.data_as(_i32p), n, _ptr(grad_seq), _ptr(dlogits),
-                                       _stream(stream)), "sp_token_logprob_bwd")
+                                       cup, n, _ptr(grad_seq), _ptr(dlogits), _stream(stream)),
+           "sp_token_logprob_bwd")
     return dlogits
 
 
@@ -306,9 +326,10 @@ def sp_attn_fwd(desc: Desc, q, k, v, o=None, lse=None, workspace=None, stream=No
             o = torch.empty((c.T_q, c.H_loc, c.head_dim), dtype=q.dtype, device=q.device)
         if lse is None:
             lse = torch.empty((c.H_loc, c.T_q), dtype=torch.float32, device=q.device)
-        ws, nb = _workspace(desc, SP_OP_FWD, q.device, workspace)
-        _check(load().sp_attn_fwd(desc.ref, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
-                                  _ptr(ws), nb, _stream(stream)), "sp_attn_fwd")
+        f, st = load().sp_attn_fwd, _stream(stream)
+        _with_workspace(desc, SP_OP_FWD, q.device, workspace,
+                        lambda ws, nb: f(desc.ref, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
+                                         ws, nb, st), "sp_attn_fwd")
     return o, lse
 
 
@@ -334,20 +355,22 @@ def sp_attn_bwd(desc: Desc, q, k, v, o, lse, dout, dq=None, dq_acc=None, dk=None
             dk = torch.empty_like(k)
         if dv is None:
             dv = torch.empty_like(v)
-        ws, nb = _workspace(desc, SP_OP_BWD, q.device, workspace)
-        _check(load().sp_attn_bwd(desc.ref, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
-                                  _ptr(dout), _ptr(dq), _ptr(dq_acc), _ptr(dk), _ptr(dv),
-                                  _ptr(ws), nb, _stream(stream)), "sp_attn_bwd")
+        f, st = load().sp_attn_bwd, _stream(stream)
+        _with_workspace(desc, SP_OP_BWD, q.device, workspace,
+                        lambda ws, nb: f(desc.ref, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
+                                         _ptr(dout), _ptr(dq), _ptr(dq_acc), _ptr(dk), _ptr(dv),
+                                         ws, nb, st), "sp_attn_bwd")
     return (dq if dq is not None else dq_acc), dk, dv
 
 
 def sp_ring_step(desc: Desc, q, k_chunk, v_chunk, o_acc, lse_acc, init: bool, o_out=None,
                  workspace=None, stream=None):
     with _alloc_on(stream):
-        ws, nb = _workspace(desc, SP_OP_RING_STEP, q.device, workspace)
-        _check(load().sp_ring_step(desc.ref, _ptr(q), _ptr(k_chunk), _ptr(v_chunk), _ptr(o_acc),
-                                   _ptr(lse_acc), 1 if init else 0, _ptr(o_out), _ptr(ws), nb,
-                                   _stream(stream)), "sp_ring_step")
+        f, st = load().sp_ring_step, _stream(stream)
+        _with_workspace(desc, SP_OP_RING_STEP, q.device, workspace,
+                        lambda ws, nb: f(desc.ref, _ptr(q), _ptr(k_chunk), _ptr(v_chunk),
+                                         _ptr(o_acc), _ptr(lse_acc), 1 if init else 0,
+                                         _ptr(o_out), ws, nb, st), "sp_ring_step")
     return o_acc, lse_acc
 
 
