@@ -324,20 +324,32 @@ double launch_bound(const WgList* lists, int n) {
 // workgroups, whose end costs a few percent at most.
 constexpr size_t kSplitItems = 4096;
 
-// log2 of the split, and the bound of the launch.
-int choose_split(const std::vector<int>& cost, const SplitModel& m, double& best) {
-  int b = 0;
+// Items from which the head-dimension-64 kernels run two workgroups a CU: their
+// tiles hold half the MFMA work of D = 128 beside the same exponentials, and
+// four wavefronts a SIMD overlap the two better (one / two workgroups: 16 heads
+// of 32768 rows, forward 2373 / 2159 us, dQ 2900 / 2726, dK/dV 4599 / 3929).
+// With fewer items the longest ones of a causal list share their CUs with the
+// next longest (8 heads of 16384 rows, 512 row items: 295 / 347 us, 12 heads,
+// 768 items: 461 / 437; dK/dV 8 heads of 4096 rows, 512 items: 87 / 91).
+constexpr size_t kTwoItems = 768;
+constexpr double kTwoGain = 0.92;
+
+// The shape of a launch of one list, and its bound.
+spk::LaunchShape choose_shape(const std::vector<int>& cost, const SplitModel& m, int D,
+                              double& best) {
+  const bool two = D == 64 && cost.size() >= kTwoItems;
+  spk::LaunchShape s{1, two};
   best = 0;
-  if (cost.size() > kSplitItems) return 0;
+  if (cost.size() > kSplitItems) return s;
   for (int i = 0; i < m.n; ++i) {
     const WgList l{cost, m, i};
-    const double t = launch_bound(&l, 1);
+    const double t = launch_bound(&l, 1) * (two && i == 0 ? kTwoGain : 1.0);
     if (i == 0 || t < best) {
-      b = i;
+      s.split = 1 << i;
       best = t;
     }
   }
-  return b;
+  return s;
 }
 
 // How a backward call runs its two work lists: one after the other, each with
@@ -348,13 +360,12 @@ int choose_split(const std::vector<int>& cost, const SplitModel& m, double& best
 // 247 -> 205, 12289 rows in segments of about 700 162 -> 143; a ring chunk of
 // 16384 rows, whose lists fill every round, is 1% slower that way.
 struct BwdPlan {
-  int split_q, split_k;
+  spk::LaunchShape q, k;
   bool one, dq_first;
 };
-BwdPlan plan_bwd(const std::vector<int>& cq, const std::vector<int>& ck) {
+BwdPlan plan_bwd(const std::vector<int>& cq, const std::vector<int>& ck, int D) {
   double tq = 0, tk = 0;
-  const int iq = choose_split(cq, kSplitDq, tq), ik = choose_split(ck, kSplitDkdv, tk);
-  BwdPlan p{1 << iq, 1 << ik, false, false};
+  BwdPlan p{choose_shape(cq, kSplitDq, D, tq), choose_shape(ck, kSplitDkdv, D, tk), false, false};
   if (cq.empty() || ck.empty() || cq.size() + ck.size() > kSplitItems) return p;
   constexpr double kLaunchUs = 4;
   double best = (tq + tk + kLaunchUs) / 1.04;
@@ -364,7 +375,7 @@ BwdPlan plan_bwd(const std::vector<int>& cq, const std::vector<int>& ck) {
     const double t = launch_bound(l, 2);
     if (t < best) {
       best = t;
-      p = BwdPlan{1 << s[0], 1 << s[1], true, l[0].us(0) > l[1].us(0)};
+      p = BwdPlan{{1 << s[0], false}, {1 << s[1], false}, true, l[0].us(0) > l[1].us(0)};
     }
   }
   return p;
@@ -883,7 +894,7 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
     a.init = init;
     a.n_items = n_items;
     double us;
-    SP_HIP(spk::launch_attn_fwd(a, list, 1 << choose_split(cost, kSplitFwd, us), p.D, ring, st));
+    SP_HIP(spk::launch_attn_fwd(a, list, choose_shape(cost, kSplitFwd, p.D, us), p.D, ring, st));
   }
   return SP_OK;
 }
@@ -984,15 +995,15 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     b.T_q = d->T_q; b.T_k = d->T_k; b.H = d->H_loc; b.Hkv = d->Hkv_loc;
     b.scale_log2 = sl2; b.scale = d->softmax_scale; b.causal = d->causal; b.direct = p.direct;
     b.n_items = (int)nb;
-    const BwdPlan plan = plan_bwd(cost_q, cost_k);
+    const BwdPlan plan = plan_bwd(cost_q, cost_k, D);
     if (by_value) std::copy(it_dq.begin(), it_dq.end(), list.v);
     if (plan.one) {
       if (by_value) std::copy(it_kv.begin(), it_kv.end(), list.v + it_dq.size());
-      SP_HIP(spk::launch_attn_bwd(a, b, list, plan.split_q, plan.split_k, plan.dq_first, D, st));
+      SP_HIP(spk::launch_attn_bwd(a, b, list, plan.q.split, plan.k.split, plan.dq_first, D, st));
     } else {
-      SP_HIP(spk::launch_attn_dq(a, list, plan.split_q, D, st));
+      SP_HIP(spk::launch_attn_dq(a, list, plan.q, D, st));
       if (by_value) std::copy(it_kv.begin(), it_kv.end(), list.v);
-      SP_HIP(spk::launch_attn_dkdv(b, list, plan.split_k, D, st));
+      SP_HIP(spk::launch_attn_dkdv(b, list, plan.k, D, st));
     }
     if (!p.direct && p.n_real > 0) {
       spk::ReduceArgs r{};

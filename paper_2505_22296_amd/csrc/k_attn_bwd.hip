@@ -62,8 +62,9 @@ struct DqStage {
   static constexpr int SMEM = NST * STAGE > XCH ? NST * STAGE : XCH;
 };
 
-// `block`: the workgroup's number among the launch's dQ workgroups.
-template <int D, int KW>
+// `block`: the workgroup's number among the launch's dQ workgroups.  TWO: at
+// most 128 VGPRs, so that two workgroups share a CU.
+template <int D, int KW, bool TWO>
 SP_DEV void dq_body(const DqArgs& a, const ItemList& list, u32x4* smem, int block) {
   using S = DqStage<D, KW>;
   constexpr int RW = S::RW, BN = S::BN, KS = D / 16, DB = D / 32, NST = S::NST, TPB = S::TPB;
@@ -173,21 +174,23 @@ SP_DEV void dq_body(const DqArgs& a, const ItemList& list, u32x4* smem, int bloc
       if (kt >= wave_kmax) continue;  // wholly past this wavefront's rows
       const u32x4* stg = smem + u * STAGE + kg * S::TILE;
 
-      // K and V fragments of the tile, all read before the first MFMA
+      // K and V fragments of the tile, all read before the first MFMA (TWO:
+      // V's after S, K^T's after dS, for the 128 registers; the other
+      // workgroup's wavefronts fill the waits)
       u32x4 kfr[KS], vfr[KS];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const int fo = (ks >> 1) * SUB + ((ks & 1) ? kf1 : kf0);
         kfr[ks] = stg[fo];
-        vfr[ks] = stg[S::OFF_V + fo];
+        if constexpr (!TWO) vfr[ks] = stg[S::OFF_V + fo];
       }
-      __builtin_amdgcn_sched_barrier(0);
-      // dP starts from -D, so the MFMAs leave dP - D.  At D = 128, KW = 4 fills
-      // the vector anew (16 moves a tile): held, it spills a Q fragment whose
-      // reload waits for every copy in flight (4 heads x 4096 rows: 66 -> 53
-      // us; without that spill the moves cost 2-5%)
+      if constexpr (!TWO) __builtin_amdgcn_sched_barrier(0);
+      // dP starts from -D, so the MFMAs leave dP - D.  Where registers are short
+      // the vector is filled anew (16 moves a tile): at D = 128, KW = 4, held,
+      // it spills a Q fragment whose reload waits for every copy in flight (4
+      // heads x 4096 rows: 66 -> 53 us; elsewhere the moves cost 2-5%)
       f32x16 s, dp;
-      if constexpr (KW == 4 && D == 128) {
+      if constexpr ((KW == 4 && D == 128) || TWO) {
         float nd = ndrow;
         asm volatile("" : "+v"(nd));
 #pragma unroll
@@ -197,30 +200,48 @@ SP_DEV void dq_body(const DqArgs& a, const ItemList& list, u32x4* smem, int bloc
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = 0.f;
+      if constexpr (!TWO) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        s = mfma32(kfr[ks], qf[ks], s);
-        dp = mfma32(vfr[ks], df[ks], dp);
+        for (int ks = 0; ks < KS; ++ks) {
+          s = mfma32(kfr[ks], qf[ks], s);
+          dp = mfma32(vfr[ks], df[ks], dp);
+        }
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s = mfma32(kfr[ks], qf[ks], s);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          vfr[ks] = stg[S::OFF_V + (ks >> 1) * SUB + ((ks & 1) ? kf1 : kf0)];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) dp = mfma32(vfr[ks], df[ks], dp);
       }
       // K^T fragments of the dQ product, read while dS is formed
       const uint16_t* stg16 = (const uint16_t*)stg;
       u32x4 ktr[DB * 2];
+      auto read_kt = [&] {
 #pragma unroll
-      for (int d = 0; d < DB; ++d)
+        for (int d = 0; d < DB; ++d)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          const int o = d * SUB * 8 + ks * 16 * 32;
-          const u32x2 lo = lds_tr16(stg16 + kt0 + o), hi = lds_tr16(stg16 + kt1 + o);
-          ktr[d * 2 + ks] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-        }
-      __builtin_amdgcn_sched_barrier(0);
+          for (int ks = 0; ks < 2; ++ks) {
+            const int o = d * SUB * 8 + ks * 16 * 32;
+            const u32x2 lo = lds_tr16(stg16 + kt0 + o), hi = lds_tr16(stg16 + kt1 + o);
+            ktr[d * 2 + ks] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+          }
+      };
+      if constexpr (!TWO) {
+        read_kt();
+        __builtin_amdgcn_sched_barrier(0);
+      }
       const bool need_mask = (kt < k0) | (kt + BN > k1) | (a.causal & (kt + BN - 1 > wr0 + delta));
       if (need_mask) {
+        // keys [lo, hi) of the lane half's, counted from kt + 8 hh
+        const int lo = k0 - kt - hh * 8;
+        const int hi = (a.causal ? min(k1, row + delta + 1) : k1) - kt - hh * 8;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          int key = kt + c_row_of(r, hh);
-          bool ok = key >= k0 && key < k1 && (!a.causal || key <= row + delta);
-          s[r] = ok ? s[r] : neg_inf();
+          const int key = c_row_of(r, 0);
+          s[r] = (key >= lo && key < hi) ? s[r] : neg_inf();
         }
       }
       float ds[16];
@@ -231,6 +252,10 @@ SP_DEV void dq_body(const DqArgs& a, const ItemList& list, u32x4* smem, int bloc
       }
       u32x4 b0 = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
       u32x4 b1 = pack_bf16x8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
+      if constexpr (TWO) {
+        __builtin_amdgcn_sched_barrier(0);
+        read_kt();
+      }
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
@@ -298,10 +323,10 @@ SP_DEV void dq_body(const DqArgs& a, const ItemList& list, u32x4* smem, int bloc
   }
 }
 
-template <int D, int KW>
-__global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a, ItemList list) {
+template <int D, int KW, bool TWO>
+__global__ __launch_bounds__(NTQ, TWO ? 4 : 1) void attn_dq_kernel(DqArgs a, ItemList list) {
   __shared__ u32x4 smem[DqStage<D, KW>::SMEM];
-  dq_body<D, KW>(a, list, smem, blockIdx.x);
+  dq_body<D, KW, TWO>(a, list, smem, blockIdx.x);
 }
 
 // ---------------------------------------------------------------- dK / dV
@@ -319,13 +344,15 @@ __global__ __launch_bounds__(NTQ, 1) void attn_dq_kernel(DqArgs a, ItemList list
 // P exchange has one slot per stage, so the loop unrolled over three groups
 // addresses both with immediate offsets.
 constexpr int NPF = kDkdvWaves / 2;  // wavefront pairs per workgroup
-constexpr int TPBF = 2;              // chunks per group (barrier interval)
-constexpr int NSTF = 3 * TPBF;       // resident chunks
-constexpr int NXF = NSTF;            // P exchange slots (one per stage)
 static_assert(kDkdvBN == 32 * NPF, "dkdv tiling");
 
-template <int D>
+template <int D, bool TWO>
 struct DkdvStage {
+  // chunks per group (barrier interval); one where the LDS of two workgroups
+  // shares a CU
+  static constexpr int TPBF = TWO ? 1 : 2;
+  static constexpr int NSTF = 3 * TPBF;  // resident chunks
+  static constexpr int NXF = NSTF;       // P exchange slots (one per stage)
   static constexpr int BQ = kDkdvBQ;
   static constexpr int SUB = BQ * 4;            // chunks per sub-tile [BQ][32]
   static constexpr int RB = BQ * (D / 8) / 64;  // 1 KB blocks of a tile
@@ -342,11 +369,12 @@ struct DkdvStage {
 // sequence, D = 128, RG = 1 / 2: 1024 rows 33 / 24 us, 4096 rows 102 / 68,
 // 16384 rows 480 / 587 us): pair p owns keys k0 + 32 (p % (NPF / RG)) ..
 // +32 and row group p / (NPF / RG), the chunks c with c % RG == its row group.
-template <int D, bool PWAVE, int RG>
+template <int D, bool PWAVE, int RG, bool TWO>
 SP_DEV void dkdv_body(const DkdvArgs& a, const int32_t (&it)[kItemInts], u32x4* smem, int w,
                       int lane) {
+  using S = DkdvStage<D, TWO>;
+  constexpr int TPBF = S::TPBF, NSTF = S::NSTF;
   static_assert(TPBF % RG == 0, "every row group has a chunk in every group of chunks");
-  using S = DkdvStage<D>;
   constexpr int BQ = S::BQ, KS = D / 16, DB = D / 32, SUB = S::SUB, NBW = S::NBW;
   constexpr int STAGE = S::STAGE;
   const int k0 = it[0], k1 = it[1], qb = it[2], qe = it[3], delta = it[4], head = it[5],
@@ -587,7 +615,7 @@ SP_DEV void dkdv_body(const DkdvArgs& a, const int32_t (&it)[kItemInts], u32x4* 
 
 // `block`: the workgroup's number among the launch's dK/dV workgroups; `base`:
 // the first dK/dV item in the list.
-template <int D, int RG>
+template <int D, int RG, bool TWO>
 SP_DEV void dkdv_wg(const DkdvArgs& a, const ItemList& list, int base, u32x4* smem, int block) {
   int32_t it[kItemInts];
   int pos, sub;
@@ -606,15 +634,16 @@ SP_DEV void dkdv_wg(const DkdvArgs& a, const ItemList& list, int base, u32x4* sm
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (w < NPF)
-    dkdv_body<D, true, RG>(a, it, smem, w, lane);
+    dkdv_body<D, true, RG, TWO>(a, it, smem, w, lane);
   else
-    dkdv_body<D, false, RG>(a, it, smem, w, lane);
+    dkdv_body<D, false, RG, TWO>(a, it, smem, w, lane);
 }
 
-template <int D, int RG>
-__global__ __launch_bounds__(64 * 2 * NPF, 1) void attn_dkdv_kernel(DkdvArgs a, ItemList list) {
-  __shared__ u32x4 smem[DkdvStage<D>::SMEM];
-  dkdv_wg<D, RG>(a, list, 0, smem, blockIdx.x);
+template <int D, int RG, bool TWO>
+__global__ __launch_bounds__(64 * 2 * NPF, TWO ? 4 : 1) void attn_dkdv_kernel(DkdvArgs a,
+                                                                             ItemList list) {
+  __shared__ u32x4 smem[DkdvStage<D, TWO>::SMEM];
+  dkdv_wg<D, RG, TWO>(a, list, 0, smem, blockIdx.x);
 }
 
 // -------------------------------------------------- dQ and dK / dV together
@@ -630,44 +659,53 @@ __global__ __launch_bounds__(NTQ, 1) void attn_bwd_kernel(DqArgs a, DkdvArgs b, 
                                                           int n_first, int dq_first) {
   static_assert(NTQ == 64 * 2 * NPF, "one workgroup size");
   using Q = DqStage<D, KW>;
-  using K = DkdvStage<D>;
+  using K = DkdvStage<D, false>;
   __shared__ u32x4 smem[Q::SMEM > K::SMEM ? Q::SMEM : K::SMEM];
   const bool first = (int)blockIdx.x < n_first;
   const int block = first ? blockIdx.x : blockIdx.x - n_first;
   if (first == (dq_first != 0))
-    dq_body<D, KW>(a, list, smem, block);
+    dq_body<D, KW, false>(a, list, smem, block);
   else
-    dkdv_wg<D, RG>(b, list, a.n_items, smem, block);
+    dkdv_wg<D, RG, false>(b, list, a.n_items, smem, block);
 }
 
 }  // namespace
 
-template <int KW>
-static hipError_t launch_dq(const DqArgs& a, const ItemList& list, int D, hipStream_t st) {
-  const dim3 grid(split_grid(a.n_items, KW)), block(NTQ);
-  if (D == 128) return sp_launch(kKDq, attn_dq_kernel<128, KW>, grid, block, st, a, list);
-  return sp_launch(kKDq, attn_dq_kernel<64, KW>, grid, block, st, a, list);
+template <int D, int KW, bool TWO>
+static hipError_t launch_dq(const DqArgs& a, const ItemList& list, hipStream_t st) {
+  return sp_launch(kKDq, attn_dq_kernel<D, KW, TWO>, dim3(split_grid(a.n_items, KW)), dim3(NTQ), st,
+                   a, list);
 }
 
-hipError_t launch_attn_dq(const DqArgs& a, const ItemList& list, int split, int D,
+hipError_t launch_attn_dq(const DqArgs& a, const ItemList& list, LaunchShape s, int D,
                           hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  if (split == 4) return launch_dq<4>(a, list, D, st);
-  if (split == 2) return launch_dq<2>(a, list, D, st);
-  return launch_dq<1>(a, list, D, st);
+  if (D == 128) {
+    if (s.split == 4) return launch_dq<128, 4, false>(a, list, st);
+    if (s.split == 2) return launch_dq<128, 2, false>(a, list, st);
+    return launch_dq<128, 1, false>(a, list, st);
+  }
+  if (s.split == 4) return launch_dq<64, 4, false>(a, list, st);
+  if (s.split == 2) return launch_dq<64, 2, false>(a, list, st);
+  if (s.two) return launch_dq<64, 1, true>(a, list, st);
+  return launch_dq<64, 1, false>(a, list, st);
 }
 
-template <int RG>
-static hipError_t launch_dkdv(const DkdvArgs& a, const ItemList& list, int D, hipStream_t st) {
-  const dim3 g(split_grid(a.n_items, RG)), b(64 * 2 * NPF);
-  if (D == 128) return sp_launch(kKDkdv, attn_dkdv_kernel<128, RG>, g, b, st, a, list);
-  return sp_launch(kKDkdv, attn_dkdv_kernel<64, RG>, g, b, st, a, list);
+template <int D, int RG, bool TWO>
+static hipError_t launch_dkdv(const DkdvArgs& a, const ItemList& list, hipStream_t st) {
+  return sp_launch(kKDkdv, attn_dkdv_kernel<D, RG, TWO>, dim3(split_grid(a.n_items, RG)),
+                   dim3(64 * 2 * NPF), st, a, list);
 }
 
-hipError_t launch_attn_dkdv(const DkdvArgs& a, const ItemList& list, int split, int D,
+hipError_t launch_attn_dkdv(const DkdvArgs& a, const ItemList& list, LaunchShape s, int D,
                             hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  return split == 2 ? launch_dkdv<2>(a, list, D, st) : launch_dkdv<1>(a, list, D, st);
+  if (D == 128)
+    return s.split == 2 ? launch_dkdv<128, 2, false>(a, list, st)
+                        : launch_dkdv<128, 1, false>(a, list, st);
+  if (s.split == 2) return launch_dkdv<64, 2, false>(a, list, st);
+  if (s.two) return launch_dkdv<64, 1, true>(a, list, st);
+  return launch_dkdv<64, 1, false>(a, list, st);
 }
 
 template <int KW, int RG>

@@ -76,8 +76,9 @@ struct FwdStage {
 // rows, key group w / RW the tiles n * KW + w / RW.  An item's rows are split
 // over KW workgroups (of 256 / KW rows each), all on the item's XCD, one
 // after the other, the last rows (the longest under a causal mask) first.
-template <int D, bool MERGE, int KW>
-__global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a, ItemList list) {
+// TWO: at most 128 VGPRs, so that two workgroups share a CU.
+template <int D, bool MERGE, int KW, bool TWO>
+__global__ __launch_bounds__(NT, TWO ? 4 : 1) void attn_fwd_kernel(FwdArgs a, ItemList list) {
   using S = FwdStage<D, KW>;
   constexpr int RW = S::RW, BN = S::BN, NST = S::NST, TPB = S::TPB;
   constexpr int KS = D / 16;   // MFMA k-steps over D
@@ -240,30 +241,38 @@ __global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a, ItemList lis
       for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
         for (int g = 0; g < G; ++g) s[g] = mfma32(kfr[g * KS + ks], qf[ks], s[g]);
-      // V^T fragments of this tile, read while the softmax runs
+      // V^T fragments of this tile, read while the softmax runs (TWO: after it,
+      // for the 128 registers)
       const uint16_t* stg16 = (const uint16_t*)stg;
       u32x4 vfr[DB * 2 * G];
+      auto read_v = [&](int ks0, int ks1) {
 #pragma unroll
-      for (int d = 0; d < DB; ++d)
+        for (int d = 0; d < DB; ++d)
 #pragma unroll
-        for (int ks = 0; ks < 2 * G; ++ks) {
-          const int o = d * SUB * 8 + ks * 16 * 32;
-          const u32x2 lo = lds_tr16(stg16 + vt0 + o), hi = lds_tr16(stg16 + vt1 + o);
-          vfr[d * 2 * G + ks] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-        }
-      __builtin_amdgcn_sched_barrier(0);
+          for (int ks = ks0; ks < ks1; ++ks) {
+            const int o = d * SUB * 8 + ks * 16 * 32;
+            const u32x2 lo = lds_tr16(stg16 + vt0 + o), hi = lds_tr16(stg16 + vt1 + o);
+            vfr[d * 2 * G + ks] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+          }
+      };
+      if constexpr (!TWO) {
+        read_v(0, 2 * G);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       if (pf) issue(n + NST - TPB);
 
       // ---- mask (only on edge / diagonal tiles)
       const bool need_mask = (kt < k0) | (kt + BN > k1) | (a.causal & (kt + BN - 1 > wr0 + delta));
       if (need_mask) {
+        // keys [lo, hi) of the lane half's, counted from kt + 8 hh
+        const int lo = k0 - kt - hh * 8;
+        const int hi = (a.causal ? min(k1, row + delta + 1) : k1) - kt - hh * 8;
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            int key = kt + g * 32 + c_row_of(r, hh);
-            bool ok = key >= k0 && key < k1 && (!a.causal || key <= row + delta);
-            if (!ok) s[g][r] = neg_inf();
+            const int key = g * 32 + c_row_of(r, 0);
+            if (key < lo || key >= hi) s[g][r] = neg_inf();
           }
       }
 
@@ -312,6 +321,10 @@ __global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a, ItemList lis
       l_part += (ps[0] + ps[1]) + (ps[2] + ps[3]);
 
       // ---- O^T += V^T P^T
+      if constexpr (TWO) {
+        __builtin_amdgcn_sched_barrier(0);
+        read_v(0, 2 * G);
+      }
 #pragma unroll
       for (int ks = 0; ks < 2 * G; ++ks)
 #pragma unroll
@@ -420,23 +433,25 @@ __global__ __launch_bounds__(NT, 1) void attn_fwd_kernel(FwdArgs a, ItemList lis
 
 }  // namespace
 
-template <int KW>
-static hipError_t launch_fwd(const FwdArgs& a, const ItemList& list, int D, bool merge,
-                             hipStream_t st) {
+template <int D, int KW, bool TWO>
+static hipError_t launch_fwd(const FwdArgs& a, const ItemList& list, bool merge, hipStream_t st) {
   const dim3 grid(split_grid(a.n_items, KW)), block(NT);
-  if (D == 128)
-    return merge ? sp_launch(kKFwd, attn_fwd_kernel<128, true, KW>, grid, block, st, a, list)
-                 : sp_launch(kKFwd, attn_fwd_kernel<128, false, KW>, grid, block, st, a, list);
-  return merge ? sp_launch(kKFwd, attn_fwd_kernel<64, true, KW>, grid, block, st, a, list)
-               : sp_launch(kKFwd, attn_fwd_kernel<64, false, KW>, grid, block, st, a, list);
+  return merge ? sp_launch(kKFwd, attn_fwd_kernel<D, true, KW, TWO>, grid, block, st, a, list)
+               : sp_launch(kKFwd, attn_fwd_kernel<D, false, KW, TWO>, grid, block, st, a, list);
 }
 
-hipError_t launch_attn_fwd(const FwdArgs& a, const ItemList& list, int split, int D, bool merge,
+hipError_t launch_attn_fwd(const FwdArgs& a, const ItemList& list, LaunchShape s, int D, bool merge,
                            hipStream_t st) {
   if (a.n_items <= 0) return hipSuccess;
-  if (split == 4) return launch_fwd<4>(a, list, D, merge, st);
-  if (split == 2) return launch_fwd<2>(a, list, D, merge, st);
-  return launch_fwd<1>(a, list, D, merge, st);
+  if (D == 128) {
+    if (s.split == 4) return launch_fwd<128, 4, false>(a, list, merge, st);
+    if (s.split == 2) return launch_fwd<128, 2, false>(a, list, merge, st);
+    return launch_fwd<128, 1, false>(a, list, merge, st);
+  }
+  if (s.split == 4) return launch_fwd<64, 4, false>(a, list, merge, st);
+  if (s.split == 2) return launch_fwd<64, 2, false>(a, list, merge, st);
+  if (s.two) return launch_fwd<64, 1, true>(a, list, merge, st);
+  return launch_fwd<64, 1, false>(a, list, merge, st);
 }
 
 }  // namespace spk

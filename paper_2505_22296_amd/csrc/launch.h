@@ -191,10 +191,15 @@ hipError_t launch_rowdot(const void* o, const void* dout, const float* lse, floa
 hipError_t launch_reduce_kv(const float* part_k, const float* part_v, void* dk, void* dv,
                             const ReduceArgs& a, hipStream_t st);
 
-// `split` workgroups an item (1, 2 or 4): 256 / split rows each
-hipError_t launch_attn_fwd(const FwdArgs& a, const ItemList& list, int split, int D, bool merge, hipStream_t st);
-hipError_t launch_attn_dq(const DqArgs& a, const ItemList& list, int split, int D, hipStream_t st);
-hipError_t launch_attn_dkdv(const DkdvArgs& a, const ItemList& list, int split, int D, hipStream_t st);
+// How a launch runs its items: `split` workgroups an item (1, 2 or 4; dK/dV 1
+// or 2), and whether two workgroups share a CU (head dimension 64, unsplit).
+struct LaunchShape {
+  int split;
+  bool two;
+};
+hipError_t launch_attn_fwd(const FwdArgs& a, const ItemList& list, LaunchShape s, int D, bool merge, hipStream_t st);
+hipError_t launch_attn_dq(const DqArgs& a, const ItemList& list, LaunchShape s, int D, hipStream_t st);
+hipError_t launch_attn_dkdv(const DkdvArgs& a, const ItemList& list, LaunchShape s, int D, hipStream_t st);
 // dQ and dK/dV in one launch; (split_q, split_k) one of (4, 2), (2, 1),
 // (1, 1).  `dq_first`: the dQ workgroups come first.
 hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, const ItemList& list, int split_q,

@@ -4,7 +4,8 @@ edges of the split tiles, one key, empty segments, dummy slots, the ring merge
 and the dQ accumulator, against the fp64 oracle at the parity bars.  The
 number of items (segments x heads) and their length decide the split: a
 handful of items are split finest, about a hundred in two, several hundred
-short ones not at all."""
+short ones not at all; at head dimension 64 768 items and more run two
+workgroups a CU."""
 import numpy as np
 import pytest
 
@@ -25,6 +26,7 @@ CASES = {
     "two": (EDGES + [250, 160, 200, 129, 140], 4, 1, 2),
     "two_full": ([256] * 25, 4, 0, 0),
     "none": (EDGES * 3, 7, 0, 0),
+    "two_a_cu": ([33, 1, 65, 40] * 18, 11, 1, 3),
 }
 
 
@@ -74,7 +76,7 @@ def test_split_items(sp, name, D, causal):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("T,H", [(1, 1), (97, 2), (300, 3), (257, 60), (200, 300)])
+@pytest.mark.parametrize("T,H", [(1, 1), (97, 2), (300, 3), (257, 60), (200, 300), (33, 800)])
 def test_split_ring_merge(sp, T, H, D):
     """Two ring steps over two KV chunks (the second shorter than one stage of
     keys) against the oracle over all keys; the first chunk's keys are hidden
