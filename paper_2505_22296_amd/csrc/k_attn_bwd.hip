@@ -186,11 +186,11 @@ SP_DEV void dq_body(const DqArgs& a, const ItemList& list, u32x4* smem, int bloc
       }
       if constexpr (!TWO) __builtin_amdgcn_sched_barrier(0);
       // dP starts from -D, so the MFMAs leave dP - D.  Where registers are short
-      // the vector is filled anew (16 moves a tile): at D = 128, KW = 4, held,
-      // it spills a Q fragment whose reload waits for every copy in flight (4
-      // heads x 4096 rows: 66 -> 53 us; elsewhere the moves cost 2-5%)
+      // the vector is filled anew (16 moves a tile): at D = 128, KW > 1, held,
+      // it spills Q fragments whose reloads wait for every copy in flight (4
+      // heads x 4096 rows, KW = 4: 66 -> 53 us; elsewhere the moves cost 2-5%)
       f32x16 s, dp;
-      if constexpr ((KW == 4 && D == 128) || TWO) {
+      if constexpr ((KW > 1 && D == 128) || TWO) {
         float nd = ndrow;
         asm volatile("" : "+v"(nd));
 #pragma unroll
