@@ -128,27 +128,46 @@ __global__ __launch_bounds__(kLB) void seq_sum_kernel(LossArgs a, const float* _
 }
 
 // dlogits[t, v] = g * (1[v == label] - exp(x - lse)), g = grad_seq[seq(t)].
+// HBM-bound (logits read once, dlogits written once).  A workgroup takes kBwdU
+// loads a thread, all in flight before the first store, of 16 KB of one row;
+// the grid walks a row's parts, then the next row, so that the chip reads and
+// writes a few neighbouring rows at a time, and few rows fill it too.  One
+// workgroup a row with one load in flight: 4096 x 152064 logits 441 us, 150 x
+// 152064 53; so: 397 (6.3 TB/s) and 17; two or four such pieces a workgroup,
+// or eight loads a thread, 1-10% slower.
+constexpr int kBwdU = 4;
 __global__ __launch_bounds__(kLB) void token_logprob_bwd_kernel(LossArgs a, const u32x4* __restrict__ logits,
                                                                 const int32_t* __restrict__ labels,
                                                                 const float* __restrict__ lse,
                                                                 const float* __restrict__ grad_seq,
-                                                                u32x4* __restrict__ dlogits) {
-  const int t = blockIdx.x;
+                                                                u32x4* __restrict__ dlogits,
+                                                                int parts) {
+  const int t = blockIdx.x / parts, part = blockIdx.x - t * parts;
   const int nch = a.V / 8;
   const int64_t base = (int64_t)t * nch;
   const int lab = labels[t];
   const int sq = seq_of(a, t);
   const bool live = sq >= 0 && lab != a.ignore_index && lab >= 0 && lab < a.V;
+  const int c0 = part * (kLB * kBwdU) + threadIdx.x;
   if (!live) {
-    for (int c = threadIdx.x; c < nch; c += kLB) dlogits[base + c] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int u = 0; u < kBwdU; ++u)
+      if (c0 + u * kLB < nch) st_stream(u32x4{0u, 0u, 0u, 0u}, &dlogits[base + c0 + u * kLB]);
     return;
   }
+  u32x4 v[kBwdU];
+#pragma unroll
+  for (int u = 0; u < kBwdU; ++u)
+    if (c0 + u * kLB < nch) v[u] = ld_stream(&logits[base + c0 + u * kLB]);
   const float g = grad_seq[sq];
   const float b = lse[t] * kLog2e;
   const float ng = -g;
-  for (int c = threadIdx.x; c < nch; c += kLB) {
+#pragma unroll
+  for (int u = 0; u < kBwdU; ++u) {
+    const int c = c0 + u * kLB;
+    if (c >= nch) break;
     float x[8];
-    decode8(ld_stream(&logits[base + c]), x);
+    decode8(v[u], x);
     float d[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -222,8 +241,10 @@ hipError_t launch_token_logprob_bwd(const LossArgs& a, const void* logits, const
                                     const float* lse, const float* grad_seq, void* dlogits,
                                     hipStream_t st) {
   if (a.T <= 0) return hipSuccess;
-  return sp_launch(kKLogprobBwd, token_logprob_bwd_kernel, dim3(a.T), dim3(kLB), st, a,
-                   (const u32x4*)logits, labels, lse, grad_seq, (u32x4*)dlogits);
+  const int parts = (a.V / 8 + kLB * kBwdU - 1) / (kLB * kBwdU);
+  // (a grid past 2^32 threads would take logits and gradients of 270 GB)
+  return sp_launch(kKLogprobBwd, token_logprob_bwd_kernel, dim3((unsigned)a.T * parts), dim3(kLB), st,
+                   a, (const u32x4*)logits, labels, lse, grad_seq, (u32x4*)dlogits, parts);
 }
 
 hipError_t launch_loss_reduce(const LossReduceArgs& a, const float* ps, const float* refs,
