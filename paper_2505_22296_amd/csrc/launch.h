@@ -63,6 +63,10 @@ struct PackArgs {
   int sp, T, Hs, Hd, nch;  // nch = 16-byte chunks per head row (D / 8)
   int map[kMaxMap];        // pack: slot -> source head; unpack: dest head -> j*Hs + h
 };
+struct PackArgsSmall {
+  int sp, T, Hs, Hd, nch;
+  int map[64];
+};
 
 // Summing unpack: destination head g sums source slots slot[start[g]] ..
 // slot[start[g+1]-1] (each j*Hs + h, ascending).  int16 keeps the arguments
