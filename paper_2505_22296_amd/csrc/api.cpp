@@ -333,19 +333,29 @@ constexpr size_t kSplitItems = 4096;
 // 768 items: 461 / 437; dK/dV 8 heads of 4096 rows, 512 items: 87 / 91).
 constexpr size_t kTwoItems = 768;
 constexpr double kTwoGain = 0.92;
+// The same for the two-way split forward (7 heads, 12289 rows in segments of
+// about 700, 364 items: 40 -> 32.5 us; 16 heads of 5000 rows, 320: 83 -> 75; 14
+// heads of 4096 rows, 224: 50 -> 52) and for the unsplit lists of a backward in
+// one launch (the former 102 -> 94 us with 1078 items, 14 heads of 4096 rows, 672:
+// 156 -> 174).
+constexpr size_t kTwoSplitItems = 300, kTwoBwdItems = 900;
+constexpr double kTwoSplitGain = 0.86;
 
 // The shape of a launch of one list, and its bound.
 spk::LaunchShape choose_shape(const std::vector<int>& cost, const SplitModel& m, int D,
                               double& best) {
-  const bool two = D == 64 && cost.size() >= kTwoItems;
-  spk::LaunchShape s{1, two};
+  // by log2 of the split; the forward alone has the second
+  const bool two[3] = {D == 64 && cost.size() >= kTwoItems,
+                       D == 64 && cost.size() >= kTwoSplitItems && &m == &kSplitFwd, false};
+  constexpr double kGain[3] = {kTwoGain, kTwoSplitGain, 1.0};
+  spk::LaunchShape s{1, two[0]};
   best = 0;
   if (cost.size() > kSplitItems) return s;
   for (int i = 0; i < m.n; ++i) {
     const WgList l{cost, m, i};
-    const double t = launch_bound(&l, 1) * (two && i == 0 ? kTwoGain : 1.0);
+    const double t = launch_bound(&l, 1) * (two[i] ? kGain[i] : 1.0);
     if (i == 0 || t < best) {
-      s.split = 1 << i;
+      s = spk::LaunchShape{1 << i, two[i]};
       best = t;
     }
   }
@@ -372,10 +382,11 @@ BwdPlan plan_bwd(const std::vector<int>& cq, const std::vector<int>& ck, int D) 
   constexpr int kPairs[3][2] = {{0, 0}, {1, 0}, {2, 1}};
   for (const auto& s : kPairs) {
     const WgList l[2] = {{cq, kSplitDq, s[0]}, {ck, kSplitDkdv, s[1]}};
-    const double t = launch_bound(l, 2);
+    const bool two = D == 64 && s[0] == 0 && cq.size() + ck.size() >= kTwoBwdItems;
+    const double t = launch_bound(l, 2) * (two ? kTwoGain : 1.0);
     if (t < best) {
       best = t;
-      p = BwdPlan{{1 << s[0], false}, {1 << s[1], false}, true, l[0].us(0) > l[1].us(0)};
+      p = BwdPlan{{1 << s[0], two}, {1 << s[1], two}, true, l[0].us(0) > l[1].us(0)};
     }
   }
   return p;
@@ -999,7 +1010,7 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     if (by_value) std::copy(it_dq.begin(), it_dq.end(), list.v);
     if (plan.one) {
       if (by_value) std::copy(it_kv.begin(), it_kv.end(), list.v + it_dq.size());
-      SP_HIP(spk::launch_attn_bwd(a, b, list, plan.q.split, plan.k.split, plan.dq_first, D, st));
+      SP_HIP(spk::launch_attn_bwd(a, b, list, plan.q, plan.k, plan.dq_first, D, st));
     } else {
       SP_HIP(spk::launch_attn_dq(a, list, plan.q, D, st));
       if (by_value) std::copy(it_kv.begin(), it_kv.end(), list.v);

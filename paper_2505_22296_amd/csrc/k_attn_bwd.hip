@@ -654,19 +654,19 @@ __global__ __launch_bounds__(64 * 2 * NPF, TWO ? 4 : 1) void attn_dkdv_kernel(Dk
 // 125 -> 99; 14 heads of 2734 rows without a mask 247 -> 205).  Workgroups
 // [0, n_first) run the list with the longer workgroups: 28 heads of 2048 rows
 // 148 us with dQ, whose items are the longer ones there, first, 160 us last.
-template <int D, int KW, int RG>
-__global__ __launch_bounds__(NTQ, 1) void attn_bwd_kernel(DqArgs a, DkdvArgs b, ItemList list,
+template <int D, int KW, int RG, bool TWO>
+__global__ __launch_bounds__(NTQ, TWO ? 4 : 1) void attn_bwd_kernel(DqArgs a, DkdvArgs b, ItemList list,
                                                           int n_first, int dq_first) {
   static_assert(NTQ == 64 * 2 * NPF, "one workgroup size");
   using Q = DqStage<D, KW>;
-  using K = DkdvStage<D, false>;
+  using K = DkdvStage<D, TWO>;
   __shared__ u32x4 smem[Q::SMEM > K::SMEM ? Q::SMEM : K::SMEM];
   const bool first = (int)blockIdx.x < n_first;
   const int block = first ? blockIdx.x : blockIdx.x - n_first;
   if (first == (dq_first != 0))
-    dq_body<D, KW, false>(a, list, smem, block);
+    dq_body<D, KW, TWO>(a, list, smem, block);
   else
-    dkdv_wg<D, RG, false>(b, list, a.n_items, smem, block);
+    dkdv_wg<D, RG, TWO>(b, list, a.n_items, smem, block);
 }
 
 }  // namespace
@@ -708,26 +708,34 @@ hipError_t launch_attn_dkdv(const DkdvArgs& a, const ItemList& list, LaunchShape
   return launch_dkdv<64, 1, false>(a, list, st);
 }
 
-template <int KW, int RG>
+template <int D, int KW, int RG, bool TWO>
 static hipError_t launch_bwd(const DqArgs& a, const DkdvArgs& b, const ItemList& list,
-                             bool dq_first, int D, hipStream_t st) {
+                             bool dq_first, hipStream_t st) {
   // the first list's workgroups are rounded up to eight, so that the second
   // list's positions keep their XCDs
   const int nq = split_grid(a.n_items, KW), nk = split_grid(b.n_items, RG);
   const int n_first = ((dq_first ? nq : nk) + 7) / 8 * 8;
   const dim3 grid(n_first + (dq_first ? nk : nq)), block(NTQ);
-  if (D == 128)
-    return sp_launch2(kKDq, kKDkdv, attn_bwd_kernel<128, KW, RG>, grid, block, st, a, b, list,
-                      n_first, (int)dq_first);
-  return sp_launch2(kKDq, kKDkdv, attn_bwd_kernel<64, KW, RG>, grid, block, st, a, b, list,
+  return sp_launch2(kKDq, kKDkdv, attn_bwd_kernel<D, KW, RG, TWO>, grid, block, st, a, b, list,
                     n_first, (int)dq_first);
 }
 
-hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, const ItemList& list, int split_q,
-                           int split_k, bool dq_first, int D, hipStream_t st) {
-  if (split_q == 4 && split_k == 2) return launch_bwd<4, 2>(a, b, list, dq_first, D, st);
-  if (split_q == 2 && split_k == 1) return launch_bwd<2, 1>(a, b, list, dq_first, D, st);
-  if (split_q == 1 && split_k == 1) return launch_bwd<1, 1>(a, b, list, dq_first, D, st);
+hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, const ItemList& list, LaunchShape q,
+                           LaunchShape k, bool dq_first, int D, hipStream_t st) {
+  if (D == 128) {
+    if (q.split == 4 && k.split == 2)
+      return launch_bwd<128, 4, 2, false>(a, b, list, dq_first, st);
+    if (q.split == 2 && k.split == 1)
+      return launch_bwd<128, 2, 1, false>(a, b, list, dq_first, st);
+    if (q.split == 1 && k.split == 1)
+      return launch_bwd<128, 1, 1, false>(a, b, list, dq_first, st);
+    return hipErrorInvalidValue;
+  }
+  if (q.split == 4 && k.split == 2) return launch_bwd<64, 4, 2, false>(a, b, list, dq_first, st);
+  if (q.split == 2 && k.split == 1) return launch_bwd<64, 2, 1, false>(a, b, list, dq_first, st);
+  if (q.split == 1 && k.split == 1)
+    return q.two ? launch_bwd<64, 1, 1, true>(a, b, list, dq_first, st)
+                 : launch_bwd<64, 1, 1, false>(a, b, list, dq_first, st);
   return hipErrorInvalidValue;
 }
 

@@ -449,7 +449,9 @@ hipError_t launch_attn_fwd(const FwdArgs& a, const ItemList& list, LaunchShape s
     return launch_fwd<128, 1, false>(a, list, merge, st);
   }
   if (s.split == 4) return launch_fwd<64, 4, false>(a, list, merge, st);
-  if (s.split == 2) return launch_fwd<64, 2, false>(a, list, merge, st);
+  if (s.split == 2)
+    return s.two ? launch_fwd<64, 2, true>(a, list, merge, st)
+                 : launch_fwd<64, 2, false>(a, list, merge, st);
   if (s.two) return launch_fwd<64, 1, true>(a, list, merge, st);
   return launch_fwd<64, 1, false>(a, list, merge, st);
 }

@@ -196,7 +196,8 @@ hipError_t launch_reduce_kv(const float* part_k, const float* part_v, void* dk, 
                             const ReduceArgs& a, hipStream_t st);
 
 // How a launch runs its items: `split` workgroups an item (1, 2 or 4; dK/dV 1
-// or 2), and whether two workgroups share a CU (head dimension 64, unsplit).
+// or 2), and whether two workgroups share a CU (head dimension 64: unsplit
+// lists, and the forward split in two).
 struct LaunchShape {
   int split;
   bool two;
@@ -204,10 +205,10 @@ struct LaunchShape {
 hipError_t launch_attn_fwd(const FwdArgs& a, const ItemList& list, LaunchShape s, int D, bool merge, hipStream_t st);
 hipError_t launch_attn_dq(const DqArgs& a, const ItemList& list, LaunchShape s, int D, hipStream_t st);
 hipError_t launch_attn_dkdv(const DkdvArgs& a, const ItemList& list, LaunchShape s, int D, hipStream_t st);
-// dQ and dK/dV in one launch; (split_q, split_k) one of (4, 2), (2, 1),
-// (1, 1).  `dq_first`: the dQ workgroups come first.
-hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, const ItemList& list, int split_q,
-                           int split_k, bool dq_first, int D, hipStream_t st);
+// dQ and dK/dV in one launch; (q.split, k.split) one of (4, 2), (2, 1),
+// (1, 1); two workgroups a CU for (1, 1) alone, q.two.  `dq_first`: the dQ workgroups come first.
+hipError_t launch_attn_bwd(const DqArgs& a, const DkdvArgs& b, const ItemList& list, LaunchShape q,
+                           LaunchShape k, bool dq_first, int D, hipStream_t st);
 
 // Tile sizes the host scheduler must use (rows per fwd/dq item, keys per
 // dk/dv item) and the kernels' LDS pipelines.

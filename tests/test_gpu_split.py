@@ -27,6 +27,7 @@ CASES = {
     "two_full": ([256] * 25, 4, 0, 0),
     "none": (EDGES * 3, 7, 0, 0),
     "two_a_cu": ([33, 1, 65, 40] * 18, 11, 1, 3),
+    "two_a_cu_split": ([257, 30, 129, 128] * 15, 4, 1, 3),
 }
 
 
