@@ -292,37 +292,47 @@ constexpr SplitModel kSplitFwd{3, 2.0, {1.0, 1.22, 1.6}};    // steps of 64 keys
 constexpr SplitModel kSplitDq{3, 1.03, {1.0, 1.15, 1.45}};   // steps of 32 keys
 constexpr SplitModel kSplitDkdv{2, 0.72, {1.0, 1.22, 0}};    // steps of 32 rows
 
-// The workgroups of one work list split S = 2^i ways: `cost` holds the items'
-// steps, longest first.
-struct WgList {
-  const std::vector<int>& cost;
-  const SplitModel& m;
-  int i;
-  size_t size() const { return cost.size() << i; }
-  double us(size_t w) const {  // of the w-th longest
-    return (double)cost[w >> i] / (1 << i) * m.rel[i] * m.step + kStartUs;
-  }
+// A work list's items: their steps, longest first, and the steps' sum.
+struct Costs {
+  std::vector<int> c;
+  double sum = 0;
 };
 
-// Lower bound of a launch of up to two lists.
-double launch_bound(const WgList* lists, int n) {
-  double total = 0, t = 0;
-  size_t at[2] = {0, 0};
-  for (size_t w = 0;; ++w) {
-    int l = -1;
-    for (int x = 0; x < n; ++x)
-      if (at[x] < lists[x].size() && (l < 0 || lists[x].us(at[x]) > lists[l].us(at[l]))) l = x;
-    if (l < 0) break;
-    const double us = lists[l].us(at[l]++);
-    total += us;
-    if (w % kCus == 0) t = std::max(t, (double)(w / kCus + 1) * us);
+// The workgroups of one work list split S = 2^i ways.
+struct WgList {
+  const Costs& cost;
+  const SplitModel& m;
+  int i;
+  size_t size() const { return cost.c.size() << i; }
+  double us(size_t w) const {  // of the w-th longest
+    return (double)cost.c[w >> i] / (1 << i) * m.rel[i] * m.step + kStartUs;
   }
-  return std::max(t, total / kCus);
+  double total() const { return cost.sum * m.rel[i] * m.step + (double)size() * kStartUs; }
+};
+
+// Lower bounds of a launch of one list, and of two.
+double launch_bound(const WgList& l) {
+  double t = l.total() / kCus;
+  for (size_t k = 0; k * kCus < l.size(); ++k) t = std::max(t, (double)(k + 1) * l.us(k * kCus));
+  return t;
+}
+double launch_bound(const WgList& p, const WgList& q) {
+  double t = (p.total() + q.total()) / kCus;
+  // the two lists merged, an item's workgroups at a time
+  const size_t sp = size_t(1) << p.i, sq = size_t(1) << q.i;
+  for (size_t a = 0, b = 0, w = 0, k = 0; a < p.size() || b < q.size();) {
+    const bool first = b >= q.size() || (a < p.size() && p.us(a) >= q.us(b));
+    const double us = first ? p.us(a) : q.us(b);
+    (first ? a : b) += first ? sp : sq;
+    w += first ? sp : sq;
+    for (; k * kCus < w; ++k) t = std::max(t, (double)(k + 1) * us);
+  }
+  return t;
 }
 
-// Items past which nothing is split or put into one launch: 16 rounds of 256
+// Items past which nothing is put into one launch: eight rounds of 256
 // workgroups, whose end costs a few percent at most.
-constexpr size_t kSplitItems = 4096;
+constexpr size_t kOneItems = 2048;
 
 // Items from which the head-dimension-64 kernels run two workgroups a CU: their
 // tiles hold half the MFMA work of D = 128 beside the same exponentials, and
@@ -342,18 +352,16 @@ constexpr size_t kTwoSplitItems = 300, kTwoBwdItems = 900;
 constexpr double kTwoSplitGain = 0.86;
 
 // The shape of a launch of one list, and its bound.
-spk::LaunchShape choose_shape(const std::vector<int>& cost, const SplitModel& m, int D,
+spk::LaunchShape choose_shape(const Costs& cost, const SplitModel& m, int D,
                               double& best) {
   // by log2 of the split; the forward alone has the second
-  const bool two[3] = {D == 64 && cost.size() >= kTwoItems,
-                       D == 64 && cost.size() >= kTwoSplitItems && &m == &kSplitFwd, false};
+  const bool two[3] = {D == 64 && cost.c.size() >= kTwoItems,
+                       D == 64 && cost.c.size() >= kTwoSplitItems && &m == &kSplitFwd, false};
   constexpr double kGain[3] = {kTwoGain, kTwoSplitGain, 1.0};
   spk::LaunchShape s{1, two[0]};
   best = 0;
-  if (cost.size() > kSplitItems) return s;
   for (int i = 0; i < m.n; ++i) {
-    const WgList l{cost, m, i};
-    const double t = launch_bound(&l, 1) * (two[i] ? kGain[i] : 1.0);
+    const double t = launch_bound(WgList{cost, m, i}) * (two[i] ? kGain[i] : 1.0);
     if (i == 0 || t < best) {
       s = spk::LaunchShape{1 << i, two[i]};
       best = t;
@@ -373,34 +381,38 @@ struct BwdPlan {
   spk::LaunchShape q, k;
   bool one, dq_first;
 };
-BwdPlan plan_bwd(const std::vector<int>& cq, const std::vector<int>& ck, int D) {
+BwdPlan plan_bwd(const Costs& cq, const Costs& ck, int D) {
   double tq = 0, tk = 0;
   BwdPlan p{choose_shape(cq, kSplitDq, D, tq), choose_shape(ck, kSplitDkdv, D, tk), false, false};
-  if (cq.empty() || ck.empty() || cq.size() + ck.size() > kSplitItems) return p;
+  const size_t n = cq.c.size() + ck.c.size();
+  if (cq.c.empty() || ck.c.empty() || n > kOneItems) return p;
   constexpr double kLaunchUs = 4;
   double best = (tq + tk + kLaunchUs) / 1.04;
   constexpr int kPairs[3][2] = {{0, 0}, {1, 0}, {2, 1}};
   for (const auto& s : kPairs) {
-    const WgList l[2] = {{cq, kSplitDq, s[0]}, {ck, kSplitDkdv, s[1]}};
-    const bool two = D == 64 && s[0] == 0 && cq.size() + ck.size() >= kTwoBwdItems;
-    const double t = launch_bound(l, 2) * (two ? kTwoGain : 1.0);
+    const WgList q{cq, kSplitDq, s[0]}, k{ck, kSplitDkdv, s[1]};
+    const bool two = D == 64 && s[0] == 0 && n >= kTwoBwdItems;
+    const double gain = two ? kTwoGain : 1.0;
+    if ((q.total() + k.total()) / kCus * gain >= best) continue;
+    const double t = launch_bound(q, k) * gain;
     if (t < best) {
       best = t;
-      p = BwdPlan{{1 << s[0], two}, {1 << s[1], two}, true, l[0].us(0) > l[1].us(0)};
+      p = BwdPlan{{1 << s[0], two}, {1 << s[1], two}, true, q.us(0) > k.us(0)};
     }
   }
   return p;
 }
 
-std::vector<int> costs_of(const std::vector<Item>& sorted) {
-  std::vector<int> c(sorted.size());
-  for (size_t i = 0; i < c.size(); ++i) c[i] = (int)sorted[i].cost;
-  return c;
+Costs costs_of(const std::vector<Item>& sorted) {
+  Costs r;
+  r.c.resize(sorted.size());
+  for (size_t i = 0; i < r.c.size(); ++i) r.sum += r.c[i] = (int)sorted[i].cost;
+  return r;
 }
 
 // Row-tile items (forward, ring step, dQ).  Returns their steps, longest first.
-std::vector<int> schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN,
-                               bool include_empty, std::vector<int32_t>& out, size_t n_front) {
+Costs schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, int BN, bool include_empty,
+                    std::vector<int32_t>& out, size_t n_front) {
   std::vector<Item> items;
   for (int y = 0; y < p.n_real; ++y) {
     for (const Seg& g : p.segs) {
@@ -432,8 +444,8 @@ std::vector<int> schedule_rows(const sp_attn_desc* d, const Problem& p, int BM, 
 
 // Key-tile items (dK / dV).  Every key of every real head gets exactly one
 // item.  Returns their steps, longest first.
-std::vector<int> schedule_keys(const sp_attn_desc* d, const Problem& p, int BNK, int BQ,
-                               std::vector<int32_t>& out, size_t n_front) {
+Costs schedule_keys(const sp_attn_desc* d, const Problem& p, int BNK, int BQ,
+                    std::vector<int32_t>& out, size_t n_front) {
   std::vector<Item> items;
   for (int y = 0; y < p.n_real; ++y) {
     for (const Seg& g : p.segs_k) {
@@ -864,8 +876,8 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
   const bool include_empty = !ring || init || o_out;
   std::vector<int32_t> items;
   const std::vector<int32_t> fills = include_empty ? row_fills(d, p) : std::vector<int32_t>();
-  const std::vector<int> cost = schedule_rows(d, p, spk::kFwdBM, spk::kFwdBN, include_empty,
-                                              items, fills.size() / kItemInts);
+  const Costs cost = schedule_rows(d, p, spk::kFwdBM, spk::kFwdBN, include_empty, items,
+                                   fills.size() / kItemInts);
   prepend(fills, items);
   const int n_items = (int)(items.size() / kItemInts);
   hipStream_t st = (hipStream_t)stream;
@@ -954,10 +966,10 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
   // a dq_acc's dummy slots stay untouched
   const std::vector<int32_t> fq = dq ? row_fills(d, p) : std::vector<int32_t>();
   const std::vector<int32_t> fkv = key_fills(d, p);
-  const std::vector<int> cost_q =
+  const Costs cost_q =
       schedule_rows(d, p, spk::kDqBM, spk::kDqBN, true, it_dq, fq.size() / kItemInts);
   prepend(fq, it_dq);
-  const std::vector<int> cost_k =
+  const Costs cost_k =
       schedule_keys(d, p, spk::kDkdvBN, spk::kDkdvBQ, it_kv, fkv.size() / kItemInts);
   prepend(fkv, it_kv);
   const size_t na = it_dq.size() / kItemInts, nb = it_kv.size() / kItemInts;
