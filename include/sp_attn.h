@@ -36,10 +36,11 @@
  *               kernel timer of sp_profile_events); calls are reentrant.  Calls
  *               that share a workspace must be ordered on one stream.
  *   Graphs      The attention entry points (sp_attn_fwd, sp_ring_step,
- *               sp_attn_bwd) copy their host-built work lists into the
- *               workspace on every call; a HIP graph would replay that copy
- *               from freed host memory, so on a stream that is being
- *               captured they return SP_ERR_UNSUPPORTED (after argument and
+ *               sp_attn_bwd) hand their host-built work lists over in the
+ *               kernel arguments or, past 512 items, copy them into the
+ *               workspace; a HIP graph would replay that copy from freed
+ *               host memory, so on a stream that is being captured they
+ *               return SP_ERR_UNSUPPORTED (after argument and
  *               workspace validation) and enqueue nothing.  Calls with no
  *               query rows, which at most zero-fill outputs, are unaffected.
  *               Every other entry point passes its host arrays by value in
@@ -253,7 +254,7 @@ sp_status sp_attn_fwd(const sp_attn_desc* desc, const void* q, const void* k, co
  * Allocation-free forward, for callers that cannot allocate device memory or
  * pass a workspace (tight serving loops, harnesses that forbid hipMalloc):
  * the same operation, kernels and outputs as sp_attn_fwd (bit for bit), with
- * the work list kept in a library-owned device array of
+ * a work list of more than 512 items kept in a library-owned device array of
  * SP_STATIC_SCRATCH_BYTES instead of a caller workspace.  Every GPU the
  * library runs on holds its own copy of that array until the process ends;
  * its address is looked up once per device on the first call there.  The
@@ -360,8 +361,9 @@ sp_status sp_f32_to_bf16(const float* src, void* dst, int64_t n, void* stream);
  *   SP_OP_BWD, dK/dV items: {k_begin, k_end, q_begin, q_end, delta, head,
  *       kv_head, 1}.
  * A launch of few items splits each of them over S workgroups (row items: S =
- * 1, 2 or 4, 256 / S rows each), which follow each other on the item's XCD;
- * the list is the same.
+ * 2 or 4, 256 / S rows each; dK/dV items: S = 2, 64 keys each), which follow
+ * each other on the item's XCD, and a backward of few items runs both its
+ * lists in one launch; the lists are the same.
  * Writes at most `capacity` items to `items` (may be NULL) and the total
  * count to *n_items.  Not listed: the zero fills of dummy query slots (and,
  * for one query head per KV head, of KV heads no real query head reads),
@@ -444,8 +446,9 @@ sp_status sp_loss_reduce(const float* partial_sums, const float* ref_partial_sum
  * caller, every launch of kernel `id` made by THIS thread records `start` on
  * the stream of the call immediately before the kernel is launched and `stop`
  * immediately after it (hipEventRecord).  If a call launches that kernel more
- * than once, the events describe the last launch.  Pass NULL events to disarm.  This is the
- * only state the library keeps (thread-local, no allocation).
+ * than once, the events describe the last launch; where a backward runs dQ and
+ * dK/dV in one launch, the events of both ids describe it.  Pass NULL events
+ * to disarm.  This is the only state the library keeps (thread-local, no allocation).
  */
 enum {
   SP_KERNEL_ATTN_FWD = 1, /* forward / ring-step attention kernel        */

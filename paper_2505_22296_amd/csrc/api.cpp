@@ -586,9 +586,9 @@ sp_status upload(void* dst, const std::vector<int32_t>& v, hipStream_t st) {
   return SP_OK;
 }
 
-// The attention entry points upload host-built work lists on every call,
-// which a captured graph would replay from freed host memory: they refuse a
-// stream that is being captured.
+// The attention entry points copy host-built work lists that do not fit the
+// kernel arguments, which a captured graph would replay from freed host
+// memory: they refuse a stream that is being captured, whatever the list.
 sp_status refuse_capture(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess) return SP_ERR_HIP;
