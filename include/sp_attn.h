@@ -376,6 +376,19 @@ sp_status sp_attn_schedule(const sp_attn_desc* desc, int32_t op, int32_t* items,
                            int32_t* n_items);
 
 /*
+ * Introspection of the launch shapes (host only, no GPU work): how `op` would
+ * run its work items.  Writes SP_PLAN_INTS int32:
+ *   {row split, row two, key split, key two, one launch, dQ first}
+ * split: workgroups an item; two: whether two workgroups share a CU (head
+ * dimension 64); rows: the items of SP_OP_FWD / SP_OP_RING_STEP (init = 1), or
+ * dQ's, keys: dK/dV's; one launch: dQ and dK/dV run in one launch, dQ first:
+ * its workgroups are the first ones there.  The last four are 0 for the
+ * forward operations.
+ */
+#define SP_PLAN_INTS 6
+sp_status sp_attn_plan(const sp_attn_desc* desc, int32_t op, int32_t* plan);
+
+/*
  * SP-aware loss (Section 3.3, Correct Loss Calculation; Section 5.1 and
  * Listing 2).  Each rank holds a slice of the sequence, so it forms the
  * label log-probabilities of its own tokens only; the SFT loss (Eq. 1) is

@@ -4,7 +4,7 @@ sequence parallelism (arXiv 2505.22296), behind the C ABI of include/sp_attn.h.
 The Python surface mirrors the C entry points one to one; see `_lib`.
 """
 from ._lib import (Desc, SpError, load, status_string, sp_attn_workspace_size, sp_attn_schedule,
-                   sp_ulysses_pack, sp_ulysses_unpack, sp_ulysses_unpack_add, sp_attn_fwd,
+                   sp_attn_plan, sp_ulysses_pack, sp_ulysses_unpack, sp_ulysses_unpack_add, sp_attn_fwd,
                    sp_attn_fwd_static, STATIC_SCRATCH_BYTES,
                    sp_attn_bwd, sp_ring_step, sp_lse_merge, sp_f32_to_bf16, sp_profile_events,
                    sp_token_logprob, sp_token_logprob_bwd, sp_loss_reduce, SP_LOSS_SFT, SP_LOSS_DPO,
@@ -18,7 +18,7 @@ from ._lib import (Desc, SpError, load, status_string, sp_attn_workspace_size, s
 
 __all__ = [
     "Desc", "SpError", "load", "status_string", "sp_attn_workspace_size", "sp_attn_schedule",
-    "sp_ulysses_pack", "sp_ulysses_unpack", "sp_ulysses_unpack_add", "sp_attn_fwd",
+    "sp_attn_plan", "sp_ulysses_pack", "sp_ulysses_unpack", "sp_ulysses_unpack_add", "sp_attn_fwd",
     "sp_attn_fwd_static", "STATIC_SCRATCH_BYTES",
     "sp_attn_bwd", "sp_ring_step", "sp_lse_merge", "sp_f32_to_bf16", "sp_profile_events",
     "sp_token_logprob", "sp_token_logprob_bwd", "sp_loss_reduce", "SP_LOSS_SFT", "SP_LOSS_DPO",

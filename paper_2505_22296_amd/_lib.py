@@ -24,6 +24,7 @@ SP_DESC_SINGLE_SEQUENCE = 1
 SP_DESC_ROWSTATS_READY = 4
 SP_DESC_DQ_ACC_INIT = 8
 SCHED_ITEM_INTS = 8
+PLAN_INTS = 6
 
 _i32p = ctypes.POINTER(ctypes.c_int32)
 
@@ -81,6 +82,7 @@ def load() -> ctypes.CDLL:
         "sp_lse_merge": (i32, [vp, vp, vp, i32, vp, i32, i32, i32, vp, vp]),
         "sp_f32_to_bf16": (i32, [vp, vp, ctypes.c_int64, vp]),
         "sp_attn_schedule": (i32, [D, i32, _i32p, i32, _i32p]),
+        "sp_attn_plan": (i32, [D, i32, _i32p]),
         "sp_profile_events": (i32, [i32, vp, vp]),
     }
     for name, (res, args) in sig.items():
@@ -94,7 +96,8 @@ def load() -> ctypes.CDLL:
 EXPORTED = ["sp_status_string", "sp_version", "sp_ulysses_pack", "sp_ulysses_unpack",
             "sp_ulysses_unpack_add", "sp_token_logprob", "sp_token_logprob_bwd", "sp_loss_reduce",
             "sp_attn_workspace_size", "sp_attn_fwd", "sp_attn_fwd_static", "sp_attn_bwd", "sp_ring_step",
-            "sp_lse_merge", "sp_f32_to_bf16", "sp_attn_schedule", "sp_profile_events"]
+            "sp_lse_merge", "sp_f32_to_bf16", "sp_attn_schedule", "sp_attn_plan",
+            "sp_profile_events"]
 
 SP_KERNEL_ATTN_FWD, SP_KERNEL_ATTN_DQ, SP_KERNEL_ATTN_DKDV = 1, 2, 3
 SP_KERNEL_PACK, SP_KERNEL_UNPACK, SP_KERNEL_LSE_MERGE, SP_KERNEL_UNPACK_ADD = 4, 5, 6, 7
@@ -219,6 +222,14 @@ def sp_attn_schedule(desc: Desc, op: int) -> np.ndarray:
     _check(lib.sp_attn_schedule(desc.ref, op, out.ctypes.data_as(_i32p), n.value, ctypes.byref(n)),
            "sp_attn_schedule")
     return out[: n.value]
+
+
+def sp_attn_plan(desc: Desc, op: int) -> dict:
+    """Host-side launch shapes: row_split, row_two, key_split, key_two,
+    one_launch, dq_first (see include/sp_attn.h)."""
+    out = (ctypes.c_int32 * PLAN_INTS)()
+    _check(load().sp_attn_plan(desc.ref, op, out), "sp_attn_plan")
+    return dict(zip(("row_split", "row_two", "key_split", "key_two", "one_launch", "dq_first"), out))
 
 
 def sp_ulysses_pack(src, sp: int, H_dst_loc: int, head_map: Sequence[int], dst=None, stream=None):

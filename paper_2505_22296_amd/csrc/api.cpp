@@ -806,6 +806,28 @@ sp_status sp_attn_schedule(const sp_attn_desc* desc, int32_t op, int32_t* items,
   return SP_OK;
 }
 
+sp_status sp_attn_plan(const sp_attn_desc* desc, int32_t op, int32_t* plan) {
+  if (!plan) return SP_ERR_INVALID_ARG;
+  if (op != SP_OP_FWD && op != SP_OP_BWD && op != SP_OP_RING_STEP) return SP_ERR_INVALID_ARG;
+  Problem p;
+  sp_status s = validate(desc, p);
+  if (s != SP_OK) return s;
+  std::vector<int32_t> v;
+  BwdPlan b{};
+  if (op == SP_OP_BWD) {
+    const Costs q = schedule_rows(desc, p, spk::kDqBM, spk::kDqBN, true, v, 0);
+    const Costs k = schedule_keys(desc, p, spk::kDkdvBN, spk::kDkdvBQ, v, 0);
+    b = plan_bwd(q, k, p.D);
+  } else {
+    double us;
+    b.q = choose_shape(schedule_rows(desc, p, spk::kFwdBM, spk::kFwdBN, true, v, 0), kSplitFwd, p.D,
+                       us);
+  }
+  const int32_t r[SP_PLAN_INTS] = {b.q.split, b.q.two, b.k.split, b.k.two, b.one, b.dq_first};
+  std::copy(r, r + SP_PLAN_INTS, plan);
+  return SP_OK;
+}
+
 }  // extern "C"
 
 namespace {
