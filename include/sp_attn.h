@@ -296,6 +296,8 @@ sp_status sp_attn_fwd_static(const sp_attn_desc* desc, const void* q, const void
  *                            last KV chunk: the accumulator's final sum goes
  *                            straight to bf16, with no separate cast.
  * dk, dv: bf16 [T_k, Hkv_loc, D], written.
+ *         dk and dv may be the k and v buffers themselves; no other output
+ *         may overlap an input.
  * Dummy slots: dq = +0.0 (dq_acc untouched); KV heads read by no real query
  * head get dk = dv = +0.0.  Deterministic: no atomics.
  */

@@ -1042,7 +1042,11 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     b.n_items = (int)nb;
     const BwdPlan plan = plan_bwd(cost_q, cost_k, D);
     if (by_value) std::copy(it_dq.begin(), it_dq.end(), list.v);
-    if (plan.one) {
+    // dK, dV written over K, V: a key's rows are read and written by one dK/dV
+    // workgroup, but dQ reads all of them, so it ends first (same splits, same
+    // bits)
+    const bool over_kv = dk == k || dk == v || dv == k || dv == v;
+    if (plan.one && !over_kv) {
       if (by_value) std::copy(it_kv.begin(), it_kv.end(), list.v + it_dq.size());
       SP_HIP(spk::launch_attn_bwd(a, b, list, plan.q, plan.k, plan.dq_first, D, st));
     } else {
