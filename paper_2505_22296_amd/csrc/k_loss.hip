@@ -140,9 +140,10 @@ __global__ __launch_bounds__(kLB) void token_logprob_bwd_kernel(LossArgs a, cons
                                                                 const int32_t* __restrict__ labels,
                                                                 const float* __restrict__ lse,
                                                                 const float* __restrict__ grad_seq,
-                                                                u32x4* __restrict__ dlogits,
-                                                                int parts) {
-  const int t = blockIdx.x / parts, part = blockIdx.x - t * parts;
+                                                                u32x4* __restrict__ dlogits) {
+  const unsigned row = blockIdx.z * gridDim.y + blockIdx.y;
+  if (row >= (unsigned)a.T) return;
+  const int t = (int)row, part = blockIdx.x;
   const int nch = a.V / 8;
   const int64_t base = (int64_t)t * nch;
   const int lab = labels[t];
@@ -242,9 +243,12 @@ hipError_t launch_token_logprob_bwd(const LossArgs& a, const void* logits, const
                                     hipStream_t st) {
   if (a.T <= 0) return hipSuccess;
   const int parts = (a.V / 8 + kLB * kBwdU - 1) / (kLB * kBwdU);
-  // (a grid past 2^32 threads would take logits and gradients of 270 GB)
-  return sp_launch(kKLogprobBwd, token_logprob_bwd_kernel, dim3((unsigned)a.T * parts), dim3(kLB), st,
-                   a, (const u32x4*)logits, labels, lse, grad_seq, (u32x4*)dlogits, parts);
+  // x: the parts of a row, (y, z): the rows.  A grid dimension of 2^32 threads
+  // or more is refused: T * parts workgroups in one would reach that at 2^24,
+  // i.e. 8.4 million rows of 8200 logits.
+  const unsigned y = a.T < 65535 ? a.T : 65535;
+  return sp_launch(kKLogprobBwd, token_logprob_bwd_kernel, dim3(parts, y, (a.T + y - 1) / y), dim3(kLB),
+                   st, a, (const u32x4*)logits, labels, lse, grad_seq, (u32x4*)dlogits);
 }
 
 hipError_t launch_loss_reduce(const LossReduceArgs& a, const float* ps, const float* refs,

@@ -38,3 +38,27 @@ def test_gradient_of_split_rows(T, V):
     assert bool(((got - ref).abs() <= bound).all())
     if T > 2:
         assert bool((buf[2] == 0).all())
+
+
+@pytest.mark.parametrize("T", [65535, 65536, 2 * 65535 + 1, (1 << 24) + 5])
+def test_gradient_of_many_rows(T):
+    """Rows past one grid dimension (65535 workgroups), and more workgroups of
+    256 threads than one dimension holds (2^32 threads); the gradient is
+    written over the logits."""
+    import torch
+    import paper_2505_22296_amd as sp
+    V = 8
+    print(f"T={T} V={V}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    buf = torch.full((T + 2, V), 3.0, dtype=torch.bfloat16, device="cuda")
+    x = buf[1:T + 1]
+    x.copy_(torch.randn((T, V), generator=gen, device="cuda"))
+    lab = torch.randint(0, V, (T,), generator=gen, device="cuda", dtype=torch.int32)
+    lse = torch.logsumexp(x.float(), 1)
+    ref = (-0.5 * torch.exp(x.double() - lse.double()[:, None]))
+    p = ref.abs()
+    ref.scatter_add_(1, lab[:, None].long(), torch.full((T, 1), 0.5, dtype=torch.float64, device="cuda"))
+    sp.sp_token_logprob_bwd(x, lab, lse, np.array([0, T], np.int32), torch.tensor([0.5], device="cuda"), dlogits=x)
+    torch.cuda.synchronize()
+    assert bool((buf[0] == 3.0).all()) and bool((buf[T + 1] == 3.0).all())
+    assert bool(((x.double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 4e-6 * p).all())
