@@ -80,11 +80,24 @@ class KernelTimers:
         self.reserve(len(self.used) + 1)
         pair = self.pool[len(self.used)]
         self.used.append((kid, flops, nbytes, pair))
-        self.sp.sp_profile_events(kid, *pair)
+        self.sp.sp_profile_events(LIB_TIMER.get(kid, kid), *pair)
+
+    def arm_backward(self, one_launch, flops_dq, flops_dkdv, mixed=False):
+        """A backward's kernels: dQ and dK/dV, or the one launch that does the
+        work of both.  `mixed`: other backwards of the step are launched the
+        other way, so their timers are disarmed first."""
+        if self.on and mixed:
+            self.sp.sp_profile_events(self.sp.SP_KERNEL_ATTN_DQ, None, None)
+            self.sp.sp_profile_events(self.sp.SP_KERNEL_ATTN_DKDV, None, None)
+        if one_launch:
+            self.arm(ONE_LAUNCH, flops_dq + flops_dkdv)
+        else:
+            self.arm(self.sp.SP_KERNEL_ATTN_DQ, flops_dq)
+            self.arm(self.sp.SP_KERNEL_ATTN_DKDV, flops_dkdv)
 
     def disarm(self):
         for kid in KNAMES:
-            self.sp.sp_profile_events(kid, None, None)
+            self.sp.sp_profile_events(LIB_TIMER.get(kid, kid), None, None)
 
     def summary(self):
         out = {}
@@ -101,6 +114,11 @@ class KernelTimers:
 
 KNAMES = {1: "attn_fwd_kernel", 2: "attn_dq_kernel", 3: "attn_dkdv_kernel", 4: "pack_kernel",
           5: "unpack_kernel", 6: "merge_kernel", 7: "unpack_add_kernel"}
+# dQ and dK/dV in one launch: a row of its own, timed by the dK/dV timer (both
+# kernels' timers describe that launch)
+ONE_LAUNCH = 100
+KNAMES[ONE_LAUNCH] = "attn_bwd_kernel"
+LIB_TIMER = {ONE_LAUNCH: 3}
 
 
 def lib_desc(sp, sh, pos_k=None, rowstats_ready=False, dq_acc_init=False):
@@ -187,6 +205,10 @@ class Step:
             self.ws_b = torch.empty(sp.sp_attn_workspace_size(self.desc, sp.SP_OP_BWD),
                                     dtype=torch.uint8, device=dev)
             self._ulysses_setup(sh)
+        # per backward: whether dQ and dK/dV run in one launch
+        self.one_launch = [sp.sp_attn_plan(d, sp.SP_OP_BWD)["one_launch"]
+                           for d in (self.descs if self.ring else [self.desc])]
+        self.mixed = len(set(self.one_launch)) > 1
         H = nr * D
         self.flops_fwd = [4.0 * H * p for p in self.pairs]
         self.flops_dq = [6.0 * H * p for p in self.pairs]
@@ -273,14 +295,12 @@ class Step:
             # the first chunk starts the fp32 dQ accumulator, the last one
             # writes the bf16 dQ from it (no clearing, no separate cast)
             for c in range(n):
-                t.arm(sp.SP_KERNEL_ATTN_DQ, self.flops_dq[c])
-                t.arm(sp.SP_KERNEL_ATTN_DKDV, self.flops_dkdv[c])
+                t.arm_backward(self.one_launch[c], self.flops_dq[c], self.flops_dkdv[c], self.mixed)
                 sp.sp_attn_bwd(self.descs_b[c], self.q, self.k[c], self.v[c], self.o, self.lse_acc,
                                self.do, dq=self.dq if c == n - 1 else None, dq_acc=self.dq_acc,
                                dk=self.dk[c], dv=self.dv[c], workspace=self.ws_b)
         else:
-            t.arm(sp.SP_KERNEL_ATTN_DQ, self.flops_dq[0])
-            t.arm(sp.SP_KERNEL_ATTN_DKDV, self.flops_dkdv[0])
+            t.arm_backward(self.one_launch[0], self.flops_dq[0], self.flops_dkdv[0])
             sp.sp_attn_bwd(self.desc, self.q, self.k, self.v, self.o, self.lse, self.do,
                            dq=self.dq, dk=self.dk, dv=self.dv, workspace=self.ws_b)
         if self.ulysses:
