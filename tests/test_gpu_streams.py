@@ -6,7 +6,9 @@ finalize, the loss path) is run twice: on the default stream, and on a side
 stream whose queue starts with a long spin, after which the inputs are
 written on that stream.  A kernel or copy issued anywhere else would run
 before the writes and read the zeros the inputs held; since every kernel is
-deterministic, the two runs must agree bit for bit."""
+deterministic, the two runs must agree bit for bit.  Both with work lists that
+travel in the kernel arguments and with lists copied to the workspace (more
+than 512 items)."""
 import numpy as np
 import pytest
 
@@ -30,11 +32,16 @@ def _bf16(bits):
     return torch.from_numpy(np.ascontiguousarray(bits).view(np.int16)).view(torch.bfloat16).cuda()
 
 
-def _sources():
+LISTS = ["in arguments", "in workspace"]
+
+
+def _sources(sp, where):
     """Device input tensors of one small instance of every step."""
     import torch
-    sh = make_shard("streams_varlen_gqa", 300, 300, 128, 4, 0, 4, 4, 2, 2, 0, [120, 0, 150],
+    seg = [120, 0, 150] if where == "in arguments" else [2, 1] * 90 + [10]
+    sh = make_shard("streams_varlen_gqa", 300, 300, 128, 4, 0, 4, 4, 2, 2, 0, seg,
                     seed_base=5)
+    assert (len(sp.sp_attn_schedule(lib_desc(sh), sp.SP_OP_FWD)) > 512) == (where == "in workspace")
     q, k, v, do = shard_inputs(sh)
     rng = np.random.default_rng(9)
     T, V = 64, 704  # V: a multiple of 8
@@ -90,9 +97,10 @@ def _bits(t):
     return t.numpy()
 
 
-def test_side_stream_runs_after_its_own_queue(sp):
+@pytest.mark.parametrize("where", LISTS)
+def test_side_stream_runs_after_its_own_queue(sp, where):
     import torch
-    sh, src = _sources()
+    sh, src = _sources(sp, where)
     ref = {k: _bits(v) for k, v in _path(sp, sh, src).items()}
     torch.cuda.synchronize()
     work = {k: torch.zeros_like(v) for k, v in src.items()}
@@ -110,14 +118,15 @@ def test_side_stream_runs_after_its_own_queue(sp):
         assert g.shape == r.shape and np.array_equal(g, r), f"{k} differs on the side stream"
 
 
-def test_concurrent_host_threads(sp):
+@pytest.mark.parametrize("where", LISTS)
+def test_concurrent_host_threads(sp, where):
     """Two host threads run the whole path at once, each on its own stream
     (the library holds no shared mutable state: schedules and uploads are
     per call, the optional kernel timers per thread).  Each thread's outputs
     match the single-threaded run bit for bit."""
     import threading
     import torch
-    sh, src = _sources()
+    sh, src = _sources(sp, where)
     ref = {k: _bits(v) for k, v in _path(sp, sh, src).items()}
     torch.cuda.synchronize()
     results, errors = [None, None], []
@@ -145,14 +154,15 @@ def test_concurrent_host_threads(sp):
                 assert np.array_equal(o[k], r), f"{k} differs in thread {i}"
 
 
-def test_explicit_stream_argument_keeps_its_buffers(sp):
+@pytest.mark.parametrize("where", LISTS)
+def test_explicit_stream_argument_keeps_its_buffers(sp, where):
     """stream= given while the current stream is the default one: the
     wrapper's own outputs and workspaces belong to the launch stream, so
     memory the default stream allocates and overwrites while the launch
     stream is still queued behind a spin is never theirs.  The results
     match the default-stream run bit for bit."""
     import torch
-    sh, src = _sources()
+    sh, src = _sources(sp, where)
     d = lib_desc(sh)
     o_r, lse_r = sp.sp_attn_fwd(d, src["q"], src["k"], src["v"])
     g_r = sp.sp_attn_bwd(d, src["q"], src["k"], src["v"], o_r, lse_r, src["do"])
