@@ -19,6 +19,8 @@
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
+#include <iterator>
 #include <mutex>
 #include <vector>
 
@@ -285,12 +287,13 @@ void sort_items(std::vector<Item>& items, std::vector<int32_t>& out, size_t n_fr
 struct SplitModel {
   int n;  // S = 1, 2, .. 2^(n-1)
   double step, rel[3];
+  double two;  // full CUs with two workgroups each against one (D = 64)
 };
 constexpr double kStartUs = 8;
 constexpr size_t kCus = 256;
-constexpr SplitModel kSplitFwd{3, 2.0, {1.0, 1.22, 1.6}};    // steps of 64 keys
-constexpr SplitModel kSplitDq{3, 1.03, {1.0, 1.15, 1.45}};   // steps of 32 keys
-constexpr SplitModel kSplitDkdv{2, 0.72, {1.0, 1.22, 0}};    // steps of 32 rows
+constexpr SplitModel kSplitFwd{3, 2.0, {1.0, 1.22, 1.6}, 0.93};    // steps of 64 keys
+constexpr SplitModel kSplitDq{3, 1.03, {1.0, 1.15, 1.45}, 0.94};   // steps of 32 keys
+constexpr SplitModel kSplitDkdv{2, 0.72, {1.0, 1.22, 0}, 0.86};    // steps of 32 rows
 
 // A work list's items: their steps, longest first, and the steps' sum.
 struct Costs {
@@ -334,20 +337,48 @@ double launch_bound(const WgList& p, const WgList& q) {
 // workgroups, whose end costs a few percent at most.
 constexpr size_t kOneItems = 2048;
 
-// Items from which the head-dimension-64 kernels run two workgroups a CU: their
-// tiles hold half the MFMA work of D = 128 beside the same exponentials, and
-// four wavefronts a SIMD overlap the two better (one / two workgroups: 16 heads
-// of 32768 rows, forward 2373 / 2159 us, dQ 2900 / 2726, dK/dV 4599 / 3929).
-// With fewer items the longest ones of a causal list share their CUs with the
-// next longest (8 heads of 16384 rows, 512 row items: 295 / 347 us, 12 heads,
-// 768 items: 461 / 437; dK/dV 8 heads of 4096 rows, 512 items: 87 / 91).
-constexpr size_t kTwoItems = 768;
-constexpr double kTwoGain = 0.92;
+// Whether an unsplit list at head dimension 64 takes the kernels that run two
+// workgroups a CU.  The tiles hold half the MFMA work of D = 128 beside the same
+// exponentials, and four wavefronts a SIMD overlap the two better: full CUs get
+// through a list in `two` of the time (16 heads of 32768 rows, one / two:
+// forward 2428 / 2271 us, dQ 2900 / 2726, dK/dV 4599 / 3929).  But the longest
+// workgroup, alone on its CU for the whole launch otherwise, shares it: with the
+// 257th longest first, then with those that are left when the first 512 have
+// been followed by 255 others (the longest's first partner ends last), and so
+// on.  One workgroup a CU takes as long as longest-first scheduling on 256 CUs,
+// run here on every 16th item and 16 CUs.  (Forward, one / two: 8 heads of 16384
+// rows 309 / 359 us, with 32 segments of 256 rows beside it 330 / 375; 12 heads
+// of 16384 rows 500 / 470; 40 full segments of 512 rows, 8 heads, 57 / 52.  The
+// choice was the faster one in all but one of 78 lists of 26 shapes.)
+bool two_a_cu(const WgList& l) {
+  const size_t n = l.size();
+  if (n <= kCus) return false;
+  const double first = l.us(0), load = l.total() / kCus;
+  double partners = l.us(kCus);
+  for (size_t k = 3; k * kCus - 1 < n && partners < first; ++k) partners += l.us(k * kCus - 1);
+  const double shared = first + (2 * l.m.two - 1) * std::min(first, partners);
+  const double two = std::max(l.m.two * load, shared);
+  if (two < std::max(load, first)) return true;  // (no schedule is shorter)
+  if (n > kOneItems) return false;               // (past eight rounds the load decides)
+  constexpr size_t kSample = 16;
+  double cu[kCus / kSample] = {};  // the least loaded first (a heap)
+  for (size_t w = kSample / 2; w < n; w += kSample) {
+    std::pop_heap(std::begin(cu), std::end(cu), std::greater<double>());
+    std::end(cu)[-1] += l.us(w);
+    std::push_heap(std::begin(cu), std::end(cu), std::greater<double>());
+  }
+  return two < *std::max_element(std::begin(cu), std::end(cu));
+}
+constexpr double kTwoGain = 0.92;  // of a list, or a backward, that takes them
 // The same for the two-way split forward (7 heads, 12289 rows in segments of
 // about 700, 364 items: 40 -> 32.5 us; 16 heads of 5000 rows, 320: 83 -> 75; 14
 // heads of 4096 rows, 224: 50 -> 52) and for the unsplit lists of a backward in
 // one launch (the former 102 -> 94 us with 1078 items, 14 heads of 4096 rows, 672:
-// 156 -> 174).
+// 156 -> 174).  The bounds above misjudge these two (the former by 18%), so they
+// go by their number of items; where one long sequence lies beside many short
+// ones that loses (4 heads of 8192 rows and 60 segments of 200, forward 78 -> 83;
+// of 16384 rows and 100 of 100, backward 531 -> 590; whole items, one workgroup a
+// CU, two launches: 130, 637).
 constexpr size_t kTwoSplitItems = 300, kTwoBwdItems = 900;
 constexpr double kTwoSplitGain = 0.86;
 
@@ -355,7 +386,7 @@ constexpr double kTwoSplitGain = 0.86;
 spk::LaunchShape choose_shape(const Costs& cost, const SplitModel& m, int D,
                               double& best) {
   // by log2 of the split; the forward alone has the second
-  const bool two[3] = {D == 64 && cost.c.size() >= kTwoItems,
+  const bool two[3] = {D == 64 && two_a_cu(WgList{cost, m, 0}),
                        D == 64 && cost.c.size() >= kTwoSplitItems && &m == &kSplitFwd, false};
   constexpr double kGain[3] = {kTwoGain, kTwoSplitGain, 1.0};
   spk::LaunchShape s{1, two[0]};
@@ -918,7 +949,7 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
   }
   if (n_items > 0) {
     spk::FwdArgs a{};
-    spk::ItemList list;  // (items past the list's are never read)
+    spk::ItemList list{};  // (items past the list's are never read)
     if (n_items <= spk::kInlineItems) {
       std::copy(items.begin(), items.end(), list.v);
     } else {
@@ -1005,7 +1036,7 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     // for dK/dV has its list first).  Else both in one copy (they are adjacent
     // in the workspace): every host-to-device copy sits between two kernels on
     // the stream.
-    spk::ItemList list;
+    spk::ItemList list{};
     const bool by_value = na + nb <= (size_t)spk::kInlineItems;
     if (!by_value) {
       const size_t gap = (L.items_kv - L.items_dq) / sizeof(int32_t);

@@ -6,6 +6,8 @@
 // bf16 rows once with 16-byte loads (the backward also writes them once).
 #include <math.h>
 
+#include <algorithm>
+
 #include "dev_common.h"
 #include "launch.h"
 
@@ -136,46 +138,58 @@ __global__ __launch_bounds__(kLB) void seq_sum_kernel(LossArgs a, const float* _
 // 152064 53; so: 397 (6.3 TB/s) and 17; two or four such pieces a workgroup,
 // or eight loads a thread, 1-10% slower.
 constexpr int kBwdU = 4;
+// Rows of up to 12288 logits take one workgroup (PARTS false), which walks them
+// U loads a thread at a time: a second workgroup of less than half the loads
+// costs more than it hides (one workgroup and one load / parts / this, 16384
+// rows of 8200 logits 97.5 / 122 / 97.7 us, of 12000 147 / 160 / 144; 8192 rows of
+// 16392 104 / 94 / 94), and so do registers for loads that no thread has (65536
+// rows of 512: 37.6 / 41.3 / 37.9).
+constexpr int kBwdOnePart = kLB * kBwdU * 3 / 2;
+template <int U, bool PARTS>
 __global__ __launch_bounds__(kLB) void token_logprob_bwd_kernel(LossArgs a, const u32x4* __restrict__ logits,
                                                                 const int32_t* __restrict__ labels,
                                                                 const float* __restrict__ lse,
                                                                 const float* __restrict__ grad_seq,
-                                                                u32x4* __restrict__ dlogits) {
-  const unsigned row = blockIdx.z * gridDim.y + blockIdx.y;
+                                                                u32x4* __restrict__ dlogits,
+                                                                unsigned parts, unsigned nx) {
+  const unsigned block = blockIdx.y * nx + blockIdx.x;
+  const unsigned row = PARTS ? block / parts : block;
   if (row >= (unsigned)a.T) return;
-  const int t = (int)row, part = blockIdx.x;
+  const int t = (int)row, part = PARTS ? (int)(block - row * parts) : 0;
   const int nch = a.V / 8;
   const int64_t base = (int64_t)t * nch;
   const int lab = labels[t];
   const int sq = seq_of(a, t);
   const bool live = sq >= 0 && lab != a.ignore_index && lab >= 0 && lab < a.V;
-  const int c0 = part * (kLB * kBwdU) + threadIdx.x;
-  if (!live) {
+  for (int c0 = part * (kLB * U) + threadIdx.x; c0 < nch; c0 += kLB * U) {
+    if (!live) {
 #pragma unroll
-    for (int u = 0; u < kBwdU; ++u)
-      if (c0 + u * kLB < nch) st_stream(u32x4{0u, 0u, 0u, 0u}, &dlogits[base + c0 + u * kLB]);
-    return;
-  }
-  u32x4 v[kBwdU];
+      for (int u = 0; u < U; ++u)
+        if (c0 + u * kLB < nch) st_stream(u32x4{0u, 0u, 0u, 0u}, &dlogits[base + c0 + u * kLB]);
+    } else {
+      u32x4 v[U];
 #pragma unroll
-  for (int u = 0; u < kBwdU; ++u)
-    if (c0 + u * kLB < nch) v[u] = ld_stream(&logits[base + c0 + u * kLB]);
-  const float g = grad_seq[sq];
-  const float b = lse[t] * kLog2e;
-  const float ng = -g;
+      for (int u = 0; u < U; ++u)
+        if (c0 + u * kLB < nch) v[u] = ld_stream(&logits[base + c0 + u * kLB]);
+      const float g = grad_seq[sq];
+      const float b = lse[t] * kLog2e;
+      const float ng = -g;
 #pragma unroll
-  for (int u = 0; u < kBwdU; ++u) {
-    const int c = c0 + u * kLB;
-    if (c >= nch) break;
-    float x[8];
-    decode8(v[u], x);
-    float d[8];
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + u * kLB;
+        if (c >= nch) break;
+        float x[8];
+        decode8(v[u], x);
+        float d[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      d[k] = ng * __builtin_amdgcn_exp2f(__builtin_fmaf(x[k], kLog2e, -b));
-      if (c * 8 + k == lab) d[k] += g;
+        for (int k = 0; k < 8; ++k) {
+          d[k] = ng * __builtin_amdgcn_exp2f(__builtin_fmaf(x[k], kLog2e, -b));
+          if (c * 8 + k == lab) d[k] += g;
+        }
+        st_stream(pack_bf16x8(d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7]), &dlogits[base + c]);
+      }
     }
-    st_stream(pack_bf16x8(d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7]), &dlogits[base + c]);
+    if (PARTS) break;
   }
 }
 
@@ -242,13 +256,19 @@ hipError_t launch_token_logprob_bwd(const LossArgs& a, const void* logits, const
                                     const float* lse, const float* grad_seq, void* dlogits,
                                     hipStream_t st) {
   if (a.T <= 0) return hipSuccess;
-  const int parts = (a.V / 8 + kLB * kBwdU - 1) / (kLB * kBwdU);
-  // x: the parts of a row, (y, z): the rows.  A grid dimension of 2^32 threads
-  // or more is refused: T * parts workgroups in one would reach that at 2^24,
-  // i.e. 8.4 million rows of 8200 logits.
-  const unsigned y = a.T < 65535 ? a.T : 65535;
-  return sp_launch(kKLogprobBwd, token_logprob_bwd_kernel, dim3(parts, y, (a.T + y - 1) / y), dim3(kLB),
-                   st, a, (const u32x4*)logits, labels, lse, grad_seq, (u32x4*)dlogits);
+  const int nch = a.V / 8;
+  const unsigned parts = nch <= kBwdOnePart ? 1 : (nch + kLB * kBwdU - 1) / (kLB * kBwdU);
+  // A grid dimension of 2^32 threads is refused: past 2^23 workgroups the grid
+  // gets a second one.  (The rows of logits on a dimension of their own take
+  // longer to hand out: 4096 x 152064 400 -> 452 us, 65536 x 8 38 -> 67.)
+  const uint64_t n = (uint64_t)a.T * parts;
+  const unsigned x = (unsigned)std::min<uint64_t>(n, 1u << 23);
+  auto* kernel = parts > 1        ? token_logprob_bwd_kernel<kBwdU, true>
+                 : nch <= kLB     ? token_logprob_bwd_kernel<1, false>
+                 : nch <= 2 * kLB ? token_logprob_bwd_kernel<2, false>
+                                  : token_logprob_bwd_kernel<kBwdU, false>;
+  return sp_launch(kKLogprobBwd, kernel, dim3(x, (unsigned)((n + x - 1) / x)), dim3(kLB), st, a,
+                   (const u32x4*)logits, labels, lse, grad_seq, (u32x4*)dlogits, parts, x);
 }
 
 hipError_t launch_loss_reduce(const LossReduceArgs& a, const float* ps, const float* refs,

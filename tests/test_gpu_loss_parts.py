@@ -1,6 +1,7 @@
-"""The logits' gradient where a row is split over workgroups of 8192 logits:
-vocabularies one 16-byte chunk below, at and above the split, one chunk in
-all, and few long rows, against the float64 formula, with guard rows around
+"""The logits' gradient: vocabularies one 16-byte chunk below, at and above the
+lengths where a thread takes a second and a third load (2048, 4096), where the
+workgroup walks on (8192) and where the row is split over workgroups of 8192
+logits (12288), one chunk in all, and few long rows, against the float64 formula, with guard rows around
 the output.  bf16 results: half an ulp of the value (2^-9 of it), plus the
 float32 exponent's error (about 2e-6 of the value at these logits)."""
 import numpy as np
@@ -9,7 +10,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,V", [(1, 8), (5, 8184), (5, 8192), (5, 8200), (3, 16384), (3, 16392), (2, 152064),
+@pytest.mark.parametrize("T,V", [(1, 8), (5, 2048), (5, 2056), (5, 4096), (5, 4104), (5, 8184),
+                                 (5, 8192), (5, 8200), (5, 12288), (5, 12296), (3, 16384), (3, 16392), (2, 152064),
                                  (1200, 2048)])
 def test_gradient_of_split_rows(T, V):
     import torch

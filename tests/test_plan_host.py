@@ -37,3 +37,21 @@ def test_shapes_over_the_range(D):
     assert _plan(D, 17, [38517], [95], causal=False)[2:5] == (2, 0, 0)
     # nothing to do
     assert _plan(D, 1, [0])[4] == 0
+
+
+def test_two_workgroups_a_cu_by_costs():
+    """Head dimension 64, unsplit lists: two workgroups a CU where the load
+    decides, one where the longest item would share its CU, whatever the
+    number of items."""
+    f = lambda *a, **k: _plan(64, *a, op=sp.SP_OP_FWD, **k)[:2]  # noqa: E731
+    assert f(16, [32768]) == f(12, [16384]) == f(3, [65536]) == f(8, [1024] * 24) == (1, 1)
+    assert f(8, [16384]) == (1, 0)
+    # 768 items as 12 heads of 16384 rows have, but the longest among short ones
+    assert f(8, [16384] + [256] * 32) == (1, 0)
+    assert f(8, [512] * 40, causal=False) == (1, 1)
+    assert f(4, [32768] + [256] * 500) == (1, 0)  # more items than are scheduled in the model
+    # backward, two launches: dQ's 768 items like the forward's, dK/dV's 1536 are shorter
+    assert _plan(64, 8, [16384] + [256] * 32) == (1, 0, 1, 1, 0, 0)
+    assert _plan(64, 12, [16384]) == (1, 1, 1, 1, 0, 0)
+    # head dimension 128 has no such kernels
+    assert _plan(128, 16, [32768], op=sp.SP_OP_FWD)[1] == 0
