@@ -34,8 +34,8 @@ static inline int grid_for(int64_t n_threads) {
 // lines for D = 64 and 128).  Planes past 2^31 chunks take 64-bit indices.
 static constexpr int kPer = 4;  // 16-byte chunks per thread
 
-// Grid of the unpack: x = the groups of kPer heads of one tile of the plane,
-// (y, z) the tiles.
+// Grid of the unpack: x = the groups of heads of one tile of the plane, (y, z)
+// the tiles.
 static inline dim3 tile_grid(int groups, int64_t tiles) {
   const int64_t y = std::min<int64_t>(tiles, 65535);
   return dim3(groups, (unsigned)y, (unsigned)((tiles + y - 1) / y));
@@ -90,33 +90,47 @@ __global__ __launch_bounds__(kBlock) void pack_kernel(const u32x4* __restrict__ 
 }
 
 // dst[t, g, c] = src[j, t, h, c] with map[g] = j*Hs + h; blockIdx.x = group of
-// kPer heads g.  A thread copies one chunk position of kPer neighbouring heads
-// of a row, and consecutive workgroups take the other heads of the same rows:
-// the destination is written in whole rows, a few row ranges at a time (28
-// heads of 8192 rows from 8 ranks 23.4 -> 22.2 us, 40 heads from 16 ranks 32.9
-// -> 30.6 against one head per grid row).  The same order for the packs, which
-// write to every rank, and the summing unpack: -3% to +18%.
-template <typename I, typename Args>
+// P heads g.  A thread copies R chunk positions (kBlock apart in the plane) of P
+// neighbouring heads, and consecutive workgroups take the other heads of the
+// same rows: the destination is written in whole rows, a few row ranges at a
+// time (28 heads of 8192 rows from 8 ranks 23.4 -> 22.2 us, 40 heads from 16
+// ranks 32.9 -> 30.6 against one head per grid row).  The same order for the
+// packs, which write to every rank, and the summing unpack: -3% to +18%.
+// P = 4 where it divides the heads.  Else threads of the last group would have
+// fewer loads in flight (5 heads of 32768 rows, D = 128: one head per grid row
+// 17.2 us, P = 4 19.9, P = 1 15.7; 6 heads of 16384 10.1, 11.9, 10.6; 13 heads,
+// D = 64, 11.4, 12.9, 11.5): P = 1, and R = 4 up to 2^21 chunks, where a chunk a
+// thread is few rounds of wavefronts (R = 1 / 4: these 6 heads 10.6 / 9.8 us, 5
+// heads of 32768 rows, D = 64, 9.5 / 8.6; 11 heads of 131072 rows 59.7 / 64.6).
+static constexpr int64_t kUnpackSmall = int64_t(1) << 21;
+template <typename I, typename Args, int P, int R>
 __global__ __launch_bounds__(kBlock) void unpack_kernel(const u32x4* __restrict__ src,
                                                         u32x4* __restrict__ dst, Args a, int lg) {
-  const int g0 = blockIdx.x * kPer;
+  const int g0 = blockIdx.x * P;
   const I n = (I)a.T * a.nch;
-  const I e = ((I)blockIdx.z * gridDim.y + blockIdx.y) * kBlock + threadIdx.x;
-  if (e >= n) return;
-  I t;
-  int c;
-  plane_index<I>(e, a.nch, lg, t, c);
-  u32x4 v[kPer];
+  const I e0 = ((I)blockIdx.z * gridDim.y + blockIdx.y) * (kBlock * R) + threadIdx.x;
+  if (R == 1 && e0 >= n) return;
+  I t[R];
+  int c[R];
 #pragma unroll
-  for (int k = 0; k < kPer; ++k)
+  for (int r = 0; r < R; ++r) plane_index<I>(e0 + r * kBlock, a.nch, lg, t[r], c[r]);
+  u32x4 v[P][R];
+#pragma unroll
+  for (int k = 0; k < P; ++k)
     if (g0 + k < a.Hd) {
       const int s = a.map[g0 + k];
       const int j = s / a.Hs, h = s - j * a.Hs;
-      v[k] = ld_stream(&src[(((I)j * a.T + t) * a.Hs + h) * a.nch + c]);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (R == 1 || e0 + r * kBlock < n)
+          v[k][r] = ld_stream(&src[(((I)j * a.T + t[r]) * a.Hs + h) * a.nch + c[r]]);
     }
 #pragma unroll
-  for (int k = 0; k < kPer; ++k)
-    if (g0 + k < a.Hd) st_stream(v[k], &dst[(t * a.Hd + g0 + k) * a.nch + c]);
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int k = 0; k < P; ++k)
+      if (g0 + k < a.Hd && (R == 1 || e0 + r * kBlock < n))
+        st_stream(v[k][r], &dst[(t[r] * a.Hd + g0 + k) * a.nch + c[r]]);
 }
 
 // dst[t, g, c] = sum over the slots s = j*Hs + h listed for g (ascending) of
@@ -228,13 +242,23 @@ hipError_t launch_unpack_add(const void* src, void* dst, const PackAddArgs& a, h
 hipError_t launch_unpack(const void* src, void* dst, const PackArgs& a, hipStream_t st) {
   const int64_t n = (int64_t)a.T * a.nch;
   if (n == 0) return hipSuccess;
-  const dim3 grid = tile_grid((a.Hd + kPer - 1) / kPer, (n + kBlock - 1) / kBlock);
   const int lg = log2_or_neg(a.nch);
-  const bool small = fits32(std::max((int64_t)a.sp * a.Hs, (int64_t)a.Hd) * n);
+  const bool fits = fits32(std::max((int64_t)a.sp * a.Hs, (int64_t)a.Hd) * n);
+  // two heads: P = 2, R = 2 up to the same size (65536 rows, D = 128: 12.9 us
+  // with one head per grid row, 14.1 with P = 4, 12.4), P = 4 past it (262144
+  // rows 48.2, 44.0)
+  const bool few = fits && n * a.Hd <= kUnpackSmall;
+  const bool pair = a.Hd == 2 && few, by4 = a.Hd % 4 == 0 || a.Hd < 3;
+  const int P = pair ? 2 : by4 ? 4 : 1, R = pair ? 2 : !by4 && few ? 4 : 1;
+  const dim3 grid = tile_grid((a.Hd + P - 1) / P, (n + kBlock * R - 1) / (kBlock * R));
   return with_args<PackArgsSmall>(a, a.Hd, [&](const auto& b) {
     using A = std::decay_t<decltype(b)>;
-    return sp_launch(kKUnpack, small ? unpack_kernel<int, A> : unpack_kernel<int64_t, A>,
-                     grid, dim3(kBlock), st, (const u32x4*)src, (u32x4*)dst, b, lg);
+    auto* kernel = pair   ? unpack_kernel<int, A, 2, 2>
+                   : by4  ? (fits ? unpack_kernel<int, A, 4, 1> : unpack_kernel<int64_t, A, 4, 1>)
+                   : R > 1 ? unpack_kernel<int, A, 1, 4>
+                   : fits  ? unpack_kernel<int, A, 1, 1>
+                           : unpack_kernel<int64_t, A, 1, 1>;
+    return sp_launch(kKUnpack, kernel, grid, dim3(kBlock), st, (const u32x4*)src, (u32x4*)dst, b, lg);
   });
 }
 
