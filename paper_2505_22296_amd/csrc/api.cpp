@@ -949,7 +949,7 @@ static sp_status fwd_common(const sp_attn_desc* d, const void* q, const void* k,
   }
   if (n_items > 0) {
     spk::FwdArgs a{};
-    spk::ItemList list;  // (items past the list's are never read)
+    spk::ItemList list{};
     if (n_items <= spk::kInlineItems) {
       std::copy(items.begin(), items.end(), list.v);
     } else {
@@ -1036,7 +1036,7 @@ sp_status sp_attn_bwd(const sp_attn_desc* d, const void* q, const void* k, const
     // for dK/dV has its list first).  Else both in one copy (they are adjacent
     // in the workspace): every host-to-device copy sits between two kernels on
     // the stream.
-    spk::ItemList list;
+    spk::ItemList list{};
     const bool by_value = na + nb <= (size_t)spk::kInlineItems;
     if (!by_value) {
       const size_t gap = (L.items_kv - L.items_dq) / sizeof(int32_t);

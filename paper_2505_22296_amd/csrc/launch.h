@@ -109,9 +109,10 @@ static constexpr int kFillRows = 8192;  // rows (keys) per zero-fill item
 // A launch's work list by value in its kernel arguments: lists of up to
 // kInlineItems items (dQ's before dK/dV's where one launch has both) travel
 // with the launch, where `items` is null; longer ones are copied into the
-// workspace.  A copy of 2 / 8 / 16 KB and a launch took 7.0 / 9.6 / 12.7 us,
-// on host and stream alike, a launch with as much in its arguments 3.6 / 3.7 /
-// 3.9 us (one without, 2.6).
+// workspace.  Every launch carries the whole array, zero past its list (all of
+// it where the list is in the workspace): 3.9 us on host and stream alike,
+// against 2.6 without one.  Arguments of 2 / 8 KB would take 3.6 / 3.7 us, a copy
+// of 2 / 8 / 16 KB and a launch 7.0 / 9.6 / 12.7 us.
 static constexpr int kInlineItems = 512;
 struct ItemList {
   int32_t v[kInlineItems * kItemInts];
