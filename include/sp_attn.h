@@ -47,7 +47,13 @@
  *               the kernel arguments and may be recorded into a graph.
  *
  * Numerics: bf16 operands, float32 accumulation, float32 softmax statistics,
- * outputs rounded to bf16 with round-to-nearest-even.
+ * outputs rounded to bf16 with round-to-nearest-even.  Repeating a call gives
+ * the same bits.  The attention of one head is not the same bits in every
+ * call: how many groups its keys (rows) are summed in follows from all work
+ * items of the call (sp_attn_plan tells), so the same head beside other heads
+ * or segments, on a rank with another share of them, or without SP at all may
+ * differ in the last bits of its float32 sums (about one bf16 rounding of some
+ * outputs).  Calls with the same {split} in their plans agree bit for bit.
  */
 #ifndef SP_ATTN_H
 #define SP_ATTN_H
