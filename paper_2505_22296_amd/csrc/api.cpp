@@ -405,9 +405,9 @@ spk::LaunchShape choose_shape(const Costs& cost, const SplitModel& m, int D,
 // the split it would take alone, or in one launch (the list with the longer
 // workgroups first), where the second list fills the CUs that the first leaves
 // idle at its end.  One launch is taken where the model sees at least 4% in it:
-// 4 heads of 1024 rows 48 -> 31 us a call, 14 heads of 2734 rows without a mask
-// 247 -> 205, 12289 rows in segments of about 700 162 -> 143; a ring chunk of
-// 16384 rows, whose lists fill every round, is 1% slower that way.
+// 4 heads of 1024 rows 41 -> 24 us a call, 14 heads of 2734 rows without a mask
+// 245 -> 193, 7 heads of 12289 rows in segments of about 700 213 -> 171; a ring
+// chunk of 16384 rows, whose lists fill every round, is 1% slower that way.
 struct BwdPlan {
   spk::LaunchShape q, k;
   bool one, dq_first;

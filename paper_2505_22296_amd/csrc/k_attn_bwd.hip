@@ -650,8 +650,9 @@ __global__ __launch_bounds__(64 * 2 * NPF, TWO ? 4 : 1) void attn_dkdv_kernel(Dk
 // Both work lists in one launch, for launches of few workgroups: each alone
 // ends with most CUs idle behind its longest items (or a last round that
 // fills few CUs); together the second list's workgroups fill the first's
-// tail (backward calls of 4 heads, D = 128: 1024 rows 48 -> 31 us, 4096 rows
-// 125 -> 99; 14 heads of 2734 rows without a mask 247 -> 205).  Workgroups
+// tail (backward calls of 4 heads, D = 128, two launches with the same splits /
+// one: 1024 rows 41 / 24 us, 4096 rows 118 / 87; 14 heads of 2734 rows without a
+// mask 245 / 193).  Workgroups
 // [0, n_first) run the list with the longer workgroups: 28 heads of 2048 rows
 // 148 us with dQ, whose items are the longer ones there, first, 160 us last.
 template <int D, int KW, int RG, bool TWO>
