@@ -390,8 +390,9 @@ sp_status sp_attn_schedule(const sp_attn_desc* desc, int32_t op, int32_t* items,
  * split: workgroups an item; two: whether two workgroups share a CU (head
  * dimension 64); rows: the items of SP_OP_FWD / SP_OP_RING_STEP (init = 1), or
  * dQ's, keys: dK/dV's; one launch: dQ and dK/dV run in one launch, dQ first:
- * its workgroups are the first ones there.  The last four are 0 for the
- * forward operations.
+ * its workgroups are the first ones there (two launches of the same splits
+ * where dk or dv is the k or v buffer).  The last four are 0 for the forward
+ * operations.
  */
 #define SP_PLAN_INTS 6
 sp_status sp_attn_plan(const sp_attn_desc* desc, int32_t op, int32_t* plan);
